@@ -130,7 +130,7 @@ def bicgstab_bytes_per_unknown(vc_words, mixed):
 
 def kernel_sources_hash():
     h = hashlib.sha256()
-    for f in ("kernels.hpp", "helmholtz.hip"):
+    for f in ("columns.hpp", "kernels.hpp", "patch.hpp", "setup.hpp", "helmholtz.hip"):
         h.update(open(os.path.join(ROOT, "paper_2002_00756_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

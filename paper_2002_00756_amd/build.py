@@ -19,7 +19,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 # Packed fp32 instructions are switched off for all device code.
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-SOURCES = ["helmholtz.hip", "mesh.cpp"]
+SOURCES = ["helmholtz.hip", "patch_f32.hip", "patch_f64.hip", "mesh.cpp"]
 
 
 def build(verbose: bool = False) -> str:

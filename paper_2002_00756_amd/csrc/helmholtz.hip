@@ -16,14 +16,17 @@
 #include "helmholtz.h"
 #include "kernels.hpp"
 #include "mesh.hpp"
+#include "patch.hpp"
+#include "setup.hpp"
 
 using namespace hh;
 
 namespace {
 
 constexpr int kRedBlocks = 2048;  // partial sums per right-hand side for vector reductions
-constexpr int kMaxLevels = 20;    // deepest hierarchy a configuration may ask for
+constexpr int kMaxLevels = kSetupLevels;
 constexpr int kApplyChunk = 4;   // vertical levels per thread in apply / residual kernels
+constexpr size_t kLdsBytes = size_t(160) << 10;  // LDS of one workgroup
 constexpr int kSmallSweepCols = 5000;  // levels below this use narrow sweep tiles
 
 // Per-level arrays use the column-tile layout of the kernels (element (k, c)
@@ -37,6 +40,7 @@ struct LevelData {
     T* mm = nullptr;  // [nvp]
     T* kv2 = nullptr; // [nvp]     9-cell stencil only
     T* s = nullptr;   // [nvp]     weighted operator only: row weight
+    T* co = nullptr;  // [kColPlanes][ncol][places] column by column, small levels only
     T* b = nullptr;   // [B][nvp]   level >= 1 (and level 0 for float32)
     T* x = nullptr;   // [B][nvp]   level >= 1 (and level 0 for float32)
     T* t = nullptr;   // [B][nvp]   ping-pong partner of x
@@ -62,6 +66,12 @@ struct Level {
     int32_t* parent = nullptr;  // [ncol] into level + 1 (not on the coarsest)
     int32_t* pofs = nullptr;    // [3][ncol] prolongation offsets (not on the coarsest)
     int32_t* child = nullptr;   // [4][ncol] into level - 1 (not on the finest)
+    // small levels: patch size (index of kPatchShapes, -1: none) and its tables
+    int patch = -1, npatch = 0;
+    int32_t* pcol = nullptr;
+    int32_t* ppar = nullptr;
+    int32_t* pcnt = nullptr;
+    uint32_t* plnb = nullptr;
     LevelData<double> d;
     LevelData<float> f;
 };
@@ -179,7 +189,7 @@ struct helmholtz_s {
     int* hact = nullptr;
     int* hseq = nullptr;
     int* hflags = nullptr;
-    size_t ws_bytes = 0;
+    size_t ws_bytes = 0, table_bytes = 0;
     // kernel timing hook: event pairs recorded around profiled launches
     struct Prof {
         double ms = 0.0, bytes = 0.0;
@@ -208,23 +218,89 @@ struct helmholtz_s {
 
 namespace {
 
+// Patch size of a level (index of kPatchShapes), -1 if its legs run kernel by
+// kernel (k_patch). By the columns of all right-hand sides: the smallest
+// levels take the smallest patches, so that a workgroup has least to do; larger
+// ones larger patches, whose rings repeat less work. V-cycle with one patched
+// level, one right-hand side, against kernel by kernel (us, float32): C12 x 30
+// 40 / 49 (2 x 2 columns; 42 with 4 x 4), C24 x 30 42 / 53 (4 x 4; 45 with
+// 2 x 2 or 8 x 4), C32 x 70 72 / 88 (8 x 4; 87 with 4 x 4). Coarsest level,
+// four sweeps: C12 x 70 23 / 30 (2 x 2), C24 x 30 16 / 25 (4 x 4), C48 x 30
+// 35 / 33.
+int patch_kind(const helmholtz_config* c, int N, bool coarsest) {
+    const int64_t cols = 6 * int64_t(N) * N * c->max_batch;
+    if (coarsest) {
+        if (c->n_coarse > 4) return -1;
+        return cols <= 1000 ? 2 : (cols <= 6200 ? 3 : -1);
+    }
+    if (c->n_pre != 2 || c->n_post != 2) return -1;
+    return cols <= 1000 ? 0 : (cols <= 4096 ? 1 : (cols <= 40000 ? 4 : -1));
+}
+
+// Whether a patch of this size pays on columns of nz levels: the deeper ones
+// need more registers than a workgroup of that size has (the values spill:
+// coarsest level C24 x 70 52 / 36 us), or the level's traffic, multiplied by
+// the rings, outgrows what the launches cost: with 8 x 4 patches vectors of up
+// to 3 MB gain (C48 x 47 float32, 2.6 MB, 81 / 85 us; C64 x 30, 2.9 MB, 74 / 80;
+// C48 x 70, 3.9 MB, 108 / 106).
+template <typename T>
+bool patch_pays(int kind, int nz, int64_t vector_values, bool nine) {
+    constexpr bool f32 = sizeof(T) == 4;
+    switch (kind) {
+        case 0:
+        case 2: return !nine || nz <= (f32 ? 80 : 48);
+        case 1: return nz <= (nine ? (f32 ? 80 : 48) : (f32 ? HELMHOLTZ_NZ_MAX : 80));
+        case 3: return nz <= (nine ? 32 : (f32 ? 64 : 48));
+        default:
+            return vector_values * int64_t(sizeof(T)) <= (int64_t(3) << 20) &&
+                   nz <= (nine ? (f32 ? 48 : 32) : (f32 ? 80 : 64));
+    }
+}
+
+// Whether the legs of level l run on patches in one launch each (k_patch) in
+// V-cycles of precision T. A float32 handle never runs a float64 V-cycle.
+template <typename T>
+bool patch_level(const helmholtz_s* h, int l) {
+    const Level& v = h->lev[l];
+    if (v.patch < 0 || (sizeof(T) == 8 && h->cfg.mg_precision == HELMHOLTZ_FP32)) return false;
+    const int jmax = patch_levels(h->nz, !h->nine && !h->weighted);
+    return patch_pays<T>(v.patch, h->nz, int64_t(v.nvp) * h->B, h->nine) &&
+           patch_lds_bytes<T>(kPatchShapes[v.patch].ncp, jmax) <= kLdsBytes;
+}
+
 void layout(helmholtz_s* h, Carver& cv) {
     const int nz = h->nz, B = h->B;
+    // the tables of all levels come first: one copy fills them (create)
     for (int l = 0; l < h->L; ++l) {
         Level& v = h->lev[l];
         const size_t nc = size_t(v.ncol);
-        const size_t nv = size_t(v.nvp);
         v.nbr = cv.take<int32_t>(4 * nc);
         v.fface = cv.take<uint32_t>(2 * nc);
         v.parent = (l + 1 < h->L) ? cv.take<int32_t>(nc) : nullptr;
         v.pofs = (l + 1 < h->L) ? cv.take<int32_t>(3 * nc) : nullptr;
         v.child = (l > 0) ? cv.take<int32_t>(4 * nc) : nullptr;
+        if (v.patch >= 0) {
+            const size_t np = size_t(v.npatch), ncp = size_t(kPatchShapes[v.patch].ncp);
+            v.pcol = cv.take<int32_t>(np * ncp);
+            v.ppar = cv.take<int32_t>(np * ncp);
+            v.pcnt = cv.take<int32_t>(np * kPatchCounts);
+            v.plnb = cv.take<uint32_t>(np * ncp);
+        }
+    }
+    h->table_bytes = cv.off;
+    for (int l = 0; l < h->L; ++l) {
+        Level& v = h->lev[l];
+        const size_t nc = size_t(v.ncol);
+        const size_t nv = size_t(v.nvp);
+        const size_t places = size_t(kPatchLanes) * patch_levels(nz, !h->nine && !h->weighted);
+        if (patch_level<double>(h, l)) v.d.co = cv.take<double>(size_t(kColPlanes) * places * nc);
+        if (patch_level<float>(h, l)) v.f.co = cv.take<float>(size_t(kColPlanes) * places * nc);
         v.d.kh = cv.take<double>(2 * nv);
         v.d.kv = cv.take<double>(nv);
         v.d.dl = cv.take<double>(nv);
         v.d.cc = cv.take<double>(nv);
         v.d.mm = cv.take<double>(nv);
-        // float32 copies: contiguous in the same order, so one conversion per level
+        // float32 copies
         v.f.kh = cv.take<float>(6 * nv);
         v.f.kv = v.f.kh + 2 * nv;
         v.f.dl = v.f.kh + 3 * nv;
@@ -290,6 +366,9 @@ void init_shape(helmholtz_s* h, const helmholtz_config* cfg) {
         v.ncol = 6 * v.N * v.N;
         v.ncolp = (v.ncol + kTile - 1) / kTile * kTile;
         v.nvp = cfg->nz * v.ncolp;
+        v.patch = patch_kind(cfg, v.N, l == h->L - 1);
+        if (v.patch >= 0)
+            v.npatch = patch_count(v.N, kPatchShapes[v.patch].pw, kPatchShapes[v.patch].ph);
     }
     h->n = int64_t(cfg->nz) * h->lev[0].ncol;
     h->nvp = h->lev[0].nvp;
@@ -645,6 +724,56 @@ T* write_dst(const helmholtz_s* h, int l, int j, T* out, T* tmp) {
     return ((level_writes(h, l) - 1 - j) % 2 == 0) ? out : tmp;
 }
 
+// Whether they do in the present call: not with H^T; and with the timing hook
+// on, the finest level runs kernel by kernel, so that the hook finds the sweeps
+// it times.
+template <typename T>
+bool on_patches(const helmholtz_s* h, int l) {
+    return patch_level<T>(h, l) && !(h->weighted && h->adj) && !(l == 0 && h->prof_on);
+}
+
+// Vectors between two levels on patches are stored column by column: those
+// of level l (b and the solution) if l and l - 1 are such levels.
+template <typename T>
+bool vectors_by_column(const helmholtz_s* h, int l) {
+    return l > 0 && l < h->L && on_patches<T>(h, l) && on_patches<T>(h, l - 1);
+}
+
+template <typename T>
+void patch_leg(const helmholtz_s* h, int l, int leg, const T* b, const T* x, const T* xc, T* y,
+               T* bc, int batch, const int* active, hipStream_t s) {
+    const Level& v = h->lev[l];
+    PatchArgs<T> A;
+    if constexpr (std::is_same<T, double>::value) A.P.co = v.d.co;
+    else A.P.co = v.f.co;
+    A.P.col = v.pcol;
+    A.P.lnb = v.plnb;
+    A.P.cnt = v.pcnt;
+    A.P.par = v.ppar;
+    A.P.npatch = v.npatch;
+    A.ncol = v.ncol;
+    A.nz = h->nz;
+    A.nvp = v.nvp;
+    A.b = b;
+    A.x = x;
+    A.xc = xc;
+    A.y = y;
+    A.bc = bc;
+    A.nvp_c = l + 1 < h->L ? h->lev[l + 1].nvp : 0;
+    A.bcol = vectors_by_column<T>(h, l);
+    A.ccol = vectors_by_column<T>(h, l + 1);
+    A.omega = T(h->cfg.omega);
+    A.batch = batch;
+    A.active = active;
+    A.mid = sweep_mid(h->nz);
+    A.nsweep = h->cfg.n_coarse;
+    // where the kernel-by-kernel path would run k_sweep<float, 9, kProlong, 32>
+    A.om_first = sizeof(T) == 4 && !h->nine && !h->weighted && v.ncol >= kSmallSweepCols &&
+                 h->nz > 32 && h->nz <= 72;
+    A.rev = h->flip(l);
+    launch_patch<T>(v.patch, leg, h->nine, h->weighted, A, s);
+}
+
 // Level l smooths b_l into out_l (Algorithm 1), using V.t[l] as the Jacobi
 // ping-pong partner and V.b, V.x of the coarser levels.
 template <typename T>
@@ -653,6 +782,17 @@ void vcycle_level(helmholtz_s* h, const VBufs<T>& V, int l, const T* b, T* out, 
     const helmholtz_config& cfg = h->cfg;
     T* tmp = V.t[l];
     const int W = level_writes(h, l);
+    if (on_patches<T>(h, l)) {
+        const T* none = nullptr;
+        if (l == h->L - 1) {
+            patch_leg<T>(h, l, kCoarse, b, none, none, out, nullptr, batch, active, s);
+            return;
+        }
+        patch_leg<T>(h, l, kDown, b, none, none, tmp, V.b[l + 1], batch, active, s);
+        vcycle_level<T>(h, V, l + 1, V.b[l + 1], V.x[l + 1], batch, active, s);
+        patch_leg<T>(h, l, kUp, b, tmp, V.x[l + 1], out, nullptr, batch, active, s);
+        return;
+    }
     if (l == h->L - 1) {
         const T* prev = nullptr;
         for (int j = 0; j < W; ++j) {
@@ -1044,21 +1184,24 @@ int create_impl(const helmholtz_config* cfg, const double* kh, const double* kv,
     h->hflags = h->hseq + h->B;
     for (int i = 0; i < h->B; ++i) h->hseq[i] = -1;
 
-    // mesh tables of every level, built on the host and copied once
+    // mesh tables of every level, built on the host and copied at once
     const int nz = h->nz;
-    std::vector<int32_t> tab;
+    std::vector<unsigned char> tables(h->table_bytes);
+    auto host = [&](auto* device) {  // where a table's host image stands
+        return reinterpret_cast<decltype(device)>(
+            tables.data() + (reinterpret_cast<uintptr_t>(device) -
+                             reinterpret_cast<uintptr_t>(workspace)));
+    };
+    std::vector<int32_t> ft;
     for (int l = 0; l < h->L; ++l) {
         Level& v = h->lev[l];
         const size_t nc = size_t(v.ncol);
-        tab.assign(4 * nc, 0);
-        build_neighbours(v.N, tab.data());
-        std::vector<int32_t> ft(4 * nc);
-        build_face_table(v.N, tab.data(), ft.data());
-        if (hipMemcpyAsync(v.nbr, tab.data(), 4 * nc * sizeof(int32_t), hipMemcpyHostToDevice, s) !=
-            hipSuccess)
-            return fail(HELMHOLTZ_EHIP);
+        int32_t* const nbr = host(v.nbr);
+        build_neighbours(v.N, nbr);
+        ft.resize(4 * nc);
+        build_face_table(v.N, nbr, ft.data());
         // W and S faces: stored face slot * ncol + owner -> offset in the tiled kh
-        std::vector<uint32_t> ff(2 * nc);
+        uint32_t* const ff = host(v.fface);
         for (size_t c = 0; c < nc; ++c) {
             for (int w = 0; w < 2; ++w) {
                 const int32_t f = ft[(w == 0 ? 1 : 3) * nc + c];
@@ -1067,43 +1210,40 @@ int create_impl(const helmholtz_config* cfg, const double* kh, const double* kv,
                                  uint32_t((owner / kTile) * kTile * nz + owner % kTile);
             }
         }
-        if (hipMemcpyAsync(v.fface, ff.data(), 2 * nc * sizeof(uint32_t), hipMemcpyHostToDevice,
-                           s) != hipSuccess)
-            return fail(HELMHOLTZ_EHIP);
-        std::vector<int32_t> par, po;
         if (v.parent) {
-            par.resize(nc);
-            build_parent(v.N, par.data());
-            if (hipMemcpyAsync(v.parent, par.data(), nc * sizeof(int32_t), hipMemcpyHostToDevice,
-                               s) != hipSuccess)
-                return fail(HELMHOLTZ_EHIP);
+            int32_t* const par = host(v.parent);
+            build_parent(v.N, par);
             // prolongation offsets: the parent and the parents of the outward
             // E/W (W for even i, E for odd i) and N/S (S for even j, N for
             // odd j) neighbours, as tiled offsets on the coarse level
             auto tb = [&](int32_t cc) { return (cc / kTile) * kTile * nz + cc % kTile; };
-            po.resize(3 * nc);
+            int32_t* const po = host(v.pofs);
             for (size_t c = 0; c < nc; ++c) {
                 const int i = int(c % v.N), j = int((c / v.N) % v.N);
-                const int32_t ew = tab[((i & 1) ? 0 : 1) * nc + c];
-                const int32_t ns = tab[((j & 1) ? 2 : 3) * nc + c];
+                const int32_t ew = nbr[((i & 1) ? 0 : 1) * nc + c];
+                const int32_t ns = nbr[((j & 1) ? 2 : 3) * nc + c];
                 po[c] = tb(par[c]);
                 po[nc + c] = tb(par[ew]);
                 po[2 * nc + c] = tb(par[ns]);
             }
-            if (hipMemcpyAsync(v.pofs, po.data(), 3 * nc * sizeof(int32_t), hipMemcpyHostToDevice,
-                               s) != hipSuccess)
-                return fail(HELMHOLTZ_EHIP);
         }
-        if (v.child) {
-            std::vector<int32_t> ch(4 * nc);
-            build_children(v.N, ch.data());
-            if (hipMemcpyAsync(v.child, ch.data(), 4 * nc * sizeof(int32_t), hipMemcpyHostToDevice,
-                               s) != hipSuccess)
-                return fail(HELMHOLTZ_EHIP);
+        if (v.child) build_children(v.N, host(v.child));
+        if (v.patch >= 0) {
+            const PatchShape& S = kPatchShapes[v.patch];
+            int32_t* const col = host(v.pcol);
+            build_patches(v.N, nbr, S.pw, S.ph, S.depth, S.ncp, col, host(v.plnb), host(v.pcnt));
+            if (v.parent) {
+                const int32_t* par = host(v.parent);
+                int32_t* const ppar = host(v.ppar);
+                for (size_t i = 0; i < size_t(v.npatch) * S.ncp; ++i) ppar[i] = par[col[i]];
+            }
         }
-        // the host vectors must stay alive until the copies have run
-        if (hipStreamSynchronize(s) != hipSuccess) return fail(HELMHOLTZ_EHIP);
     }
+    // the host image must stay alive until the copy has run
+    if (hipMemcpyAsync(workspace, tables.data(), tables.size(), hipMemcpyHostToDevice, s) !=
+            hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return fail(HELMHOLTZ_EHIP);
 
     if (int e = set_coefficients(h, kh, kv, kv2, delta, sw, s)) return fail(e);
     *out = h;
@@ -1132,20 +1272,29 @@ int set_coefficients(helmholtz_s* h, const double* kh, const double* kv, const d
                            c.nvp, c.child, f.d.kh, f.d.kv, f.d.dl, f.d.kv2, f.d.s, c.d.kh,
                            c.d.kv, c.d.dl, c.d.kv2, c.d.s);
     }
+    // factors and float32 copies of every level, then the coefficients of the
+    // levels on patches
+    const bool f64 = h->cfg.mg_precision == HELMHOLTZ_FP64;
+    SetupLevels all{}, patched{};
+    int tiles = 0, ptiles = 0;
     for (int l = 0; l < h->L; ++l) {
-        Level& v = h->lev[l];
-        hipLaunchKernelGGL(k_factor, dim3((v.ncol + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
-                           view<double>(h, l), sweep_mid(nz), v.d.cc, v.d.mm);
-        // float32 copies, rounded once from float64 (padding included)
-        const int64_t nv = v.nvp;
-        convert<double, float>(v.d.kh, v.f.kh, 2 * nv, s);
-        convert<double, float>(v.d.kv, v.f.kv, nv, s);
-        convert<double, float>(v.d.dl, v.f.dl, nv, s);
-        convert<double, float>(v.d.cc, v.f.cc, nv, s);
-        convert<double, float>(v.d.mm, v.f.mm, nv, s);
-        if (h->nine) convert<double, float>(v.d.kv2, v.f.kv2, nv, s);
-        if (h->weighted) convert<double, float>(v.d.s, v.f.s, nv, s);
+        const Level& v = h->lev[l];
+        SetupLevel S{v.ncol, v.nvp, tiles, v.fface, v.d.kh, v.d.kv, v.d.dl, v.d.kv2, v.d.s,
+                     f64 ? v.d.cc : nullptr, f64 ? v.d.mm : nullptr, v.f.kh, v.f.kv, v.f.dl,
+                     v.f.cc, v.f.mm, v.f.kv2, v.f.s, v.d.co, v.f.co};
+        all.lev[all.count++] = S;
+        tiles += v.ncolp / kTile;
+        if (!v.d.co && !v.f.co) continue;
+        S.tile0 = ptiles;
+        patched.lev[patched.count++] = S;
+        ptiles += v.ncolp / kTile;
     }
+    hipLaunchKernelGGL(k_factor_levels, dim3(tiles), dim3(kBlock),
+                       2 * size_t(nz) * kTile * sizeof(double), s, all, nz, sweep_mid(nz));
+    if (ptiles)
+        hipLaunchKernelGGL(k_patch_coefficients, dim3(ptiles, kColPlanes), dim3(kBlock), 0, s,
+                           patched, nz, sweep_mid(nz),
+                           kPatchLanes * patch_levels(nz, !h->nine && !h->weighted));
     if (last_error() != HELMHOLTZ_OK) return HELMHOLTZ_EHIP;
     if (hipMemcpyAsync(h->hflags, h->flags, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess)
         return HELMHOLTZ_EHIP;

@@ -9,8 +9,10 @@
 // down the adjacent face, the one whose normal is the step direction.
 #include "mesh.hpp"
 
+#include <algorithm>
 #include <array>
 #include <cstdint>
+#include <vector>
 
 namespace hh {
 namespace {
@@ -114,6 +116,46 @@ void build_children(int Nc, int32_t* child) {
                     child[s * ncc + C] =
                         int32_t(p * Nf * Nf + (2 * J + dj) * Nf + (2 * I + di));
                 }
+            }
+}
+
+void build_patches(int N, const int32_t* nbr, int pw, int ph, int depth, int ncp, int32_t* cols,
+                   uint32_t* lnbs, int32_t* cnts) {
+    const size_t ncol = 6 * size_t(N) * N, np = size_t(patch_count(N, pw, ph));
+    std::fill(lnbs, lnbs + np * ncp, 0u);
+    std::fill(cnts, cnts + np * 8, 0);
+    std::vector<int32_t> place(ncol, -1);  // column -> place in the current list
+    size_t p = 0;
+    for (int pan = 0; pan < 6; ++pan)
+        for (int j0 = 0; j0 < N; j0 += ph)
+            for (int i0 = 0; i0 < N; i0 += pw, ++p) {
+                const int w = std::min(pw, N - i0), h = std::min(ph, N - j0);
+                int32_t* col = cols + p * ncp;
+                int32_t* cnt = cnts + p * 8;
+                uint32_t* lnb = lnbs + p * ncp;
+                int n = 0;
+                auto add = [&](int32_t c) {
+                    if (place[c] < 0) {
+                        place[c] = n;
+                        col[n++] = c;
+                    }
+                };
+                for (int j = j0; j < j0 + h; ++j)
+                    for (int i = i0; i < i0 + w; ++i)
+                        add(int32_t((int64_t(pan) * N + j) * N + i));
+                cnt[4] = w;
+                cnt[0] = n;
+                for (int r = 1; r <= depth; ++r) {
+                    const int from = r == 1 ? 0 : cnt[r - 2], to = cnt[r - 1];
+                    for (int q = from; q < to; ++q)
+                        for (int d = 0; d < 4; ++d) add(nbr[d * ncol + col[q]]);
+                    cnt[r] = n;
+                }
+                for (int q = 0; q < cnt[depth - 1]; ++q)
+                    for (int d = 0; d < 4; ++d)
+                        lnb[q] |= uint32_t(place[nbr[d * ncol + col[q]]]) << (8 * d);
+                for (int q = 0; q < n; ++q) place[col[q]] = -1;
+                for (int q = n; q < ncp; ++q) col[q] = col[0];
             }
 }
 
