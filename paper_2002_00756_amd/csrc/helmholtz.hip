@@ -477,7 +477,7 @@ void launch_sweep_b(const helmholtz_s* h, int l, const T* b, const T* x, const T
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(ntile * batch), dim3(kBlock), Tile::lds_bytes(h->nz), s,
                            view<T>(h, l), b, x, xc, nvp_c, y, T(h->cfg.omega), batch, active,
-                           sweep_mid(h->nz), rev);
+                           sweep_mid(h->nz), rev, static_cast<T*>(nullptr));
     };
     // only the large levels use 32-column tiles and can stream past the cache
     constexpr bool kCanStream = TC == kTile;
@@ -550,6 +550,41 @@ void launch_sweep_m(const helmholtz_s* h, int l, const T* b, const T* x, const T
         launch_sweep_tc<T, MODE, 8>(h, l, b, x, xc, y, batch, active, s);
     else
         launch_sweep_tc<T, MODE, 32>(h, l, b, x, xc, y, batch, active, s);
+}
+
+// The first (kIoIn, from zero) or the last (kIoOut, plain) sweep of the finest
+// level with b or the result in the ABI layout, S values: 7-point operator, 32-
+// column tiles.
+template <typename T, typename S, int JMAX, int MODE, int IO>
+void launch_sweep_io_j(const helmholtz_s* h, const T* b, const T* x, T* y, S* ext, int batch,
+                       hipStream_t s) {
+    const Level& v = h->lev[0];
+    using Tile = SweepTile<T>;
+    const bool prof = MODE == kPlain && prof_begin(h, HELMHOLTZ_PROF_SWEEP_FINE, s);
+    const int rev = h->flip(0);
+    auto go = [&](auto kern) {
+        const T* xc = nullptr;
+        const int* active = nullptr;
+        hipLaunchKernelGGL(kern, dim3(v.ncolp / kTile * batch), dim3(kBlock),
+                           Tile::lds_bytes(h->nz), s, view<T>(h, 0), b, x, xc, 0, y,
+                           T(h->cfg.omega), batch, active, sweep_mid(h->nz), rev, ext);
+    };
+    if (sweep_streams_past_cache(h, 0, batch, sizeof(T)))
+        go(k_sweep<T, JMAX, MODE, kTile, kBlock, 0, false, kSym, true, S, IO>);
+    else
+        go(k_sweep<T, JMAX, MODE, kTile, kBlock, 0, false, kSym, false, S, IO>);
+    if (prof)
+        prof_end(h, HELMHOLTZ_PROF_SWEEP_FINE,
+                 7.0 * sizeof(T) * double(batch) * h->nz * v.ncol, s);
+}
+
+template <typename T, typename S, int MODE, int IO>
+void launch_sweep_io(const helmholtz_s* h, const T* b, const T* x, T* y, S* ext, int batch,
+                     hipStream_t s) {
+    const int jn = (h->nz + 7) / 8;
+    if (jn <= 4) launch_sweep_io_j<T, S, 4, MODE, IO>(h, b, x, y, ext, batch, s);
+    else if (jn <= 9) launch_sweep_io_j<T, S, 9, MODE, IO>(h, b, x, y, ext, batch, s);
+    else launch_sweep_io_j<T, S, 15, MODE, IO>(h, b, x, y, ext, batch, s);
 }
 
 // Levels too small to fill the GPU are bound by the latency of a few dependent
@@ -653,8 +688,7 @@ void launch_apply(const helmholtz_s* h, int l, const T* x, T* y, int batch, int 
             switch (dot) {
                 case kDotXY: go(k_apply_lds<T, kDotXY, kApplyChunk, NT, PX, K2>); break;
                 case kDotWY: go(k_apply_lds<T, kDotWY, kApplyChunk, NT, PX, K2>); break;
-                case kDotWYYY: go(k_apply_lds<T, kDotWYYY, kApplyChunk, NT, PX, K2>); break;
-                default: go(k_apply_lds<T, kDotNone, kApplyChunk, NT, PX, K2>); break;
+                default: go(k_apply_lds<T, kDotWYYY, kApplyChunk, NT, PX, K2>); break;
             }
         };
         auto by_width = [&](auto nts, auto k2) {
@@ -672,42 +706,80 @@ void launch_apply(const helmholtz_s* h, int l, const T* x, T* y, int batch, int 
             switch (dot) {
                 case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kRowWT>); break;
                 case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kRowWT>); break;
-                case kDotWYYY: go(k_apply<T, kDotWYYY, kApplyChunk, false, kRowWT>); break;
-                default: go(k_apply<T, kDotNone, kApplyChunk, false, kRowWT>); break;
+                default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kRowWT>); break;
             }
         } else {
             switch (dot) {
                 case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kRowW>); break;
                 case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kRowW>); break;
-                case kDotWYYY: go(k_apply<T, kDotWYYY, kApplyChunk, false, kRowW>); break;
-                default: go(k_apply<T, kDotNone, kApplyChunk, false, kRowW>); break;
+                default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kRowW>); break;
             }
         }
     } else if (h->nine) {
         switch (dot) {
             case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, true>); break;
             case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, true>); break;
-            case kDotWYYY: go(k_apply<T, kDotWYYY, kApplyChunk, true>); break;
-            default: go(k_apply<T, kDotNone, kApplyChunk, true>); break;
+            default: go(k_apply<T, kDotWYYY, kApplyChunk, true>); break;
         }
     } else if (streams_past_cache(h, l, batch, sizeof(T))) {
         switch (dot) {
             case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kSym, true>); break;
             case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kSym, true>); break;
-            case kDotWYYY: go(k_apply<T, kDotWYYY, kApplyChunk, false, kSym, true>); break;
-            default: go(k_apply<T, kDotNone, kApplyChunk, false, kSym, true>); break;
+            default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kSym, true>); break;
         }
     } else {
         switch (dot) {
             case kDotXY: go(k_apply<T, kDotXY, kApplyChunk>); break;
             case kDotWY: go(k_apply<T, kDotWY, kApplyChunk>); break;
-            case kDotWYYY: go(k_apply<T, kDotWYYY, kApplyChunk>); break;
-            default: go(k_apply<T, kDotNone, kApplyChunk>); break;
+            default: go(k_apply<T, kDotWYYY, kApplyChunk>); break;
         }
     }
     if (prof)  // x, kh[2], kv, delta (, kv2) read; y written
         prof_end(h, HELMHOLTZ_PROF_APPLY_FINE,
                  (h->nine ? 7.0 : 6.0) * sizeof(T) * double(batch) * h->nz * v.ncol, s);
+}
+
+// y = H x on the finest level with x and y in the ABI layout.
+void launch_apply_natural(const helmholtz_s* h, const double* x, double* y, int batch,
+                          hipStream_t s) {
+    const Level& v = h->lev[0];
+    const int ntile = (v.ncol + kBlock - 1) / kBlock;
+    const int nkc = (h->nz + kApplyChunk - 1) / kApplyChunk;
+    const bool prof = prof_begin(h, HELMHOLTZ_PROF_APPLY_FINE, s);
+    const int rev = h->flip(0);
+    auto go = [&](auto kern) {
+        const double* none = nullptr;
+        hipLaunchKernelGGL(kern, dim3(ntile * nkc * batch), dim3(kBlock), 0, s,
+                           view<double>(h, 0), x, y, none, batch, nkc, cg_state(h),
+                           static_cast<const int*>(nullptr), rev);
+    };
+    // the same choice of kernel as for tiled vectors (launch_apply)
+    constexpr int KC = kApplyChunk;
+    const bool nts = streams_past_cache(h, 0, batch, sizeof(double));
+    if (v.N % kTile == 0 && !h->weighted) {
+        auto by_width = [&](auto nt, auto k2) {
+            constexpr bool NT = decltype(nt)::value, K2 = decltype(k2)::value;
+            if (v.N % 64 == 0) go(k_apply_lds<double, kDotNone, KC, NT, 64, K2, true>);
+            else go(k_apply_lds<double, kDotNone, KC, NT, 32, K2, true>);
+        };
+        if (nts) h->nine ? by_width(std::true_type{}, std::true_type{})
+                         : by_width(std::true_type{}, std::false_type{});
+        else h->nine ? by_width(std::false_type{}, std::true_type{})
+                     : by_width(std::false_type{}, std::false_type{});
+    } else if (h->weighted && h->adj) {
+        go(k_apply<double, kDotNone, KC, false, kRowWT, false, true>);
+    } else if (h->weighted) {
+        go(k_apply<double, kDotNone, KC, false, kRowW, false, true>);
+    } else if (h->nine) {
+        go(k_apply<double, kDotNone, KC, true, kSym, false, true>);
+    } else if (nts) {
+        go(k_apply<double, kDotNone, KC, false, kSym, true, true>);
+    } else {
+        go(k_apply<double, kDotNone, KC, false, kSym, false, true>);
+    }
+    if (prof)
+        prof_end(h, HELMHOLTZ_PROF_APPLY_FINE,
+                 (h->nine ? 7.0 : 6.0) * sizeof(double) * double(batch) * h->nz * v.ncol, s);
 }
 
 // ---- V-cycle (Algorithm 1) ------------------------------------------------
@@ -732,6 +804,14 @@ bool on_patches(const helmholtz_s* h, int l) {
     return patch_level<T>(h, l) && !(h->weighted && h->adj) && !(l == 0 && h->prof_on);
 }
 
+// b and x of a V-cycle entry point in the ABI layout; wide: float64 ones of a
+// float32 V-cycle.
+struct AbiVectors {
+    const void* b;
+    void* x;
+    bool wide;
+};
+
 // Vectors between two levels on patches are stored column by column: those
 // of level l (b and the solution) if l and l - 1 are such levels.
 template <typename T>
@@ -741,7 +821,7 @@ bool vectors_by_column(const helmholtz_s* h, int l) {
 
 template <typename T>
 void patch_leg(const helmholtz_s* h, int l, int leg, const T* b, const T* x, const T* xc, T* y,
-               T* bc, int batch, const int* active, hipStream_t s) {
+               T* bc, int batch, const int* active, hipStream_t s, const AbiVectors* io) {
     const Level& v = h->lev[l];
     PatchArgs<T> A;
     if constexpr (std::is_same<T, double>::value) A.P.co = v.d.co;
@@ -760,7 +840,10 @@ void patch_leg(const helmholtz_s* h, int l, int leg, const T* b, const T* x, con
     A.y = y;
     A.bc = bc;
     A.nvp_c = l + 1 < h->L ? h->lev[l + 1].nvp : 0;
-    A.bcol = vectors_by_column<T>(h, l);
+    A.layout = vectors_by_column<T>(h, l) ? kByColumn : (io ? kAbi : kTiled);
+    A.ext_b = io ? io->b : nullptr;
+    A.ext_y = io ? io->x : nullptr;
+    A.ext_wide = io && io->wide;
     A.ccol = vectors_by_column<T>(h, l + 1);
     A.omega = T(h->cfg.omega);
     A.batch = batch;
@@ -775,29 +858,55 @@ void patch_leg(const helmholtz_s* h, int l, int leg, const T* b, const T* x, con
 }
 
 // Level l smooths b_l into out_l (Algorithm 1), using V.t[l] as the Jacobi
-// ping-pong partner and V.b, V.x of the coarser levels.
+// ping-pong partner and V.b, V.x of the coarser levels. io (level 0 only): the
+// first kernel reads b, and the last one writes the result, in the ABI layout;
+// b and out are then this level's own buffers.
 template <typename T>
 void vcycle_level(helmholtz_s* h, const VBufs<T>& V, int l, const T* b, T* out, int batch,
-                  const int* active, hipStream_t s) {
+                  const int* active, hipStream_t s, const AbiVectors* io = nullptr) {
     const helmholtz_config& cfg = h->cfg;
     T* tmp = V.t[l];
     const int W = level_writes(h, l);
     if (on_patches<T>(h, l)) {
         const T* none = nullptr;
         if (l == h->L - 1) {
-            patch_leg<T>(h, l, kCoarse, b, none, none, out, nullptr, batch, active, s);
+            patch_leg<T>(h, l, kCoarse, b, none, none, out, nullptr, batch, active, s, io);
             return;
         }
-        patch_leg<T>(h, l, kDown, b, none, none, tmp, V.b[l + 1], batch, active, s);
+        patch_leg<T>(h, l, kDown, b, none, none, tmp, V.b[l + 1], batch, active, s, io);
         vcycle_level<T>(h, V, l + 1, V.b[l + 1], V.x[l + 1], batch, active, s);
-        patch_leg<T>(h, l, kUp, b, tmp, V.x[l + 1], out, nullptr, batch, active, s);
+        patch_leg<T>(h, l, kUp, b, tmp, V.x[l + 1], out, nullptr, batch, active, s, io);
         return;
     }
+    // the first sweep from zero and the last plain one, with b and the result in
+    // the ABI layout where io is given
+    auto sweep_first = [&](T* dst) {
+        if (io && io->wide)
+            launch_sweep_io<T, double, kZero, kIoIn>(
+                h, b, nullptr, dst, static_cast<double*>(const_cast<void*>(io->b)), batch, s);
+        else if (io)
+            launch_sweep_io<T, T, kZero, kIoIn>(
+                h, b, nullptr, dst, static_cast<T*>(const_cast<void*>(io->b)), batch, s);
+        else
+            launch_sweep<T>(h, l, kZero, b, nullptr, nullptr, dst, batch, active, s);
+    };
+    auto sweep_last = [&](const T* prev, T* dst) {
+        if (io && io->wide)
+            launch_sweep_io<T, double, kPlain, kIoOut>(h, b, prev, dst,
+                                                       static_cast<double*>(io->x), batch, s);
+        else if (io)
+            launch_sweep_io<T, T, kPlain, kIoOut>(h, b, prev, dst, static_cast<T*>(io->x), batch,
+                                                  s);
+        else
+            launch_sweep<T>(h, l, kPlain, b, prev, nullptr, dst, batch, active, s);
+    };
     if (l == h->L - 1) {
         const T* prev = nullptr;
         for (int j = 0; j < W; ++j) {
             T* dst = write_dst<T>(h, l, j, out, tmp);
-            launch_sweep<T>(h, l, j == 0 ? kZero : kPlain, b, prev, nullptr, dst, batch, active, s);
+            if (j == 0) sweep_first(dst);
+            else if (j == W - 1) sweep_last(prev, dst);
+            else launch_sweep<T>(h, l, kPlain, b, prev, nullptr, dst, batch, active, s);
             prev = dst;
         }
         return;
@@ -806,7 +915,8 @@ void vcycle_level(helmholtz_s* h, const VBufs<T>& V, int l, const T* b, T* out, 
     const T* prev = nullptr;
     for (int i = 0; i < cfg.n_pre; ++i, ++j) {
         T* dst = write_dst<T>(h, l, j, out, tmp);
-        launch_sweep<T>(h, l, j == 0 ? kZero : kPlain, b, prev, nullptr, dst, batch, active, s);
+        if (j == 0) sweep_first(dst);
+        else launch_sweep<T>(h, l, kPlain, b, prev, nullptr, dst, batch, active, s);
         prev = dst;
     }
     T* cb = V.b[l + 1];
@@ -825,9 +935,23 @@ void vcycle_level(helmholtz_s* h, const VBufs<T>& V, int l, const T* b, T* out, 
         T* dst = write_dst<T>(h, l, j, out, tmp);
         int mode = kPlain;
         if (i == 0) mode = prev ? kProlong : kProlongZero;
-        launch_sweep<T>(h, l, mode, b, prev, cx, dst, batch, active, s);
+        if (i > 0 && i == cfg.n_post - 1) sweep_last(prev, dst);
+        else launch_sweep<T>(h, l, mode, b, prev, cx, dst, batch, active, s);
         prev = dst;
     }
+}
+
+// Whether a V-cycle of precision T can take b and hand out x in the ABI layout
+// within its own kernels, without conversion passes: the finest level runs on
+// patches, or begins with a sweep from zero and ends with a plain one on 32-
+// column tiles (7-point operator; the others keep the passes: two more
+// compiled forms of every sweep).
+template <typename T>
+bool abi_within(const helmholtz_s* h) {
+    const helmholtz_config& c = h->cfg;
+    if (on_patches<T>(h, 0)) return true;
+    if (h->nine || h->weighted || h->lev[0].ncol < kSmallSweepCols) return false;
+    return h->L == 1 ? c.n_coarse >= 2 : c.n_pre >= 1 && c.n_post >= 2;
 }
 
 int check_batch(const helmholtz_s* h, int32_t batch) {
@@ -1050,6 +1174,22 @@ size_t carve_levels(const helmholtz_s* h, uintptr_t base, int batch, VBufs<T>& V
     return cv.off;
 }
 
+// One V-cycle from the ABI layout to the ABI layout, in V; bt and xt are the
+// tiled vectors of the finest level.
+template <typename T, typename S>
+int vcycle_abi(helmholtz_s* h, const VBufs<T>& V, T* bt, T* xt, const S* b, S* x, int batch,
+               hipStream_t s) {
+    if (abi_within<T>(h)) {
+        const AbiVectors io{b, x, sizeof(S) != sizeof(T)};
+        vcycle_level<T>(h, V, 0, bt, xt, batch, nullptr, s, &io);
+    } else {
+        retile<S, T, true>(h, b, bt, batch, s);
+        vcycle_level<T>(h, V, 0, bt, xt, batch, nullptr, s);
+        retile<T, S, false>(h, xt, x, batch, s);
+    }
+    return last_error();
+}
+
 // One V-cycle from the ABI layout to the ABI layout with the level vectors in
 // the static scratch array (helmholtz_vcycle_noalloc).
 template <typename T>
@@ -1057,10 +1197,7 @@ int vcycle_in_scratch(helmholtz_s* h, const double* b, double* x, int batch, hip
     VBufs<T> V;
     if (carve_levels<T>(h, reinterpret_cast<uintptr_t>(h->scratch), batch, V) > kScratchBytes)
         return HELMHOLTZ_ESCRATCH;
-    retile<double, T, true>(h, b, V.b[0], batch, s);
-    vcycle_level<T>(h, V, 0, V.b[0], V.x[0], batch, nullptr, s);
-    retile<T, double, false>(h, V.x[0], x, batch, s);
-    return last_error();
+    return vcycle_abi<T, double>(h, V, V.b[0], V.x[0], b, x, batch, s);
 }
 
 // Weighted handles run the calls that take H^T with the transposed kernels.
@@ -1350,9 +1487,7 @@ int helmholtz_apply(helmholtz_t h, const double* x, double* y, int32_t batch,
     if (int e = check_batch(h, batch)) return e;
     if (!x || !y) return HELMHOLTZ_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    retile<double, double, true>(h, x, h->p, batch, s);
-    launch_apply<double>(h, 0, h->p, h->q, batch, kDotNone, nullptr, s);
-    retile<double, double, false>(h, h->q, y, batch, s);
+    launch_apply_natural(h, x, y, batch, s);
     return last_error();
 }
 
@@ -1361,17 +1496,9 @@ int helmholtz_vcycle(helmholtz_t h, const double* b, double* x, int32_t batch,
     if (int e = check_batch(h, batch)) return e;
     if (!b || !x) return HELMHOLTZ_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (h->cfg.mg_precision == HELMHOLTZ_FP64) {
-        retile<double, double, true>(h, b, h->r, batch, s);
-        if (int e = precondition(h, h->r, h->z, batch, nullptr, s)) return e;
-        retile<double, double, false>(h, h->z, x, batch, s);
-    } else {
-        const VBufs<float>& V = h->vb32;
-        retile<double, float, true>(h, b, V.b[0], batch, s);
-        if (int e = precondition(h, nullptr, nullptr, batch, nullptr, s)) return e;
-        retile<float, double, false>(h, V.x[0], x, batch, s);
-    }
-    return last_error();
+    if (h->cfg.mg_precision == HELMHOLTZ_FP64)
+        return vcycle_abi<double, double>(h, h->vb64, h->r, h->z, b, x, batch, s);
+    return vcycle_abi<float, double>(h, h->vb32, h->vb32.b[0], h->vb32.x[0], b, x, batch, s);
 }
 
 int helmholtz_vcycle_noalloc(helmholtz_t h, const double* b, double* x, int32_t batch,
@@ -1391,11 +1518,7 @@ int helmholtz_vcycle_f32(helmholtz_t h, const float* b, float* x, int32_t batch,
     if (int e = check_batch(h, batch)) return e;
     if (!b || !x) return HELMHOLTZ_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const VBufs<float>& V = h->vb32;
-    retile<float, float, true>(h, b, V.b[0], batch, s);
-    vcycle_level<float>(h, V, 0, V.b[0], V.x[0], batch, nullptr, s);
-    retile<float, float, false>(h, V.x[0], x, batch, s);
-    return last_error();
+    return vcycle_abi<float, float>(h, h->vb32, h->vb32.b[0], h->vb32.x[0], b, x, batch, s);
 }
 
 int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, double rtol,

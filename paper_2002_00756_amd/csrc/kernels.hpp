@@ -32,6 +32,12 @@ namespace hh {
 // bytes); the small LDS footprint lets up to 8 workgroups share a CU.
 enum SweepMode { kZero = 0, kPlain = 1, kProlong = 2, kProlongZero = 3 };
 
+// kIoIn: b comes from ext in the ABI layout and is left in b, tiled, for the
+// kernels that follow; kIoOut: the new iterate goes to ext in the ABI layout
+// instead of y. (A V-cycle entry point then needs no conversion passes: on
+// C192 x 30, float32, 280 -> 267 us.)
+enum { kIoNone = 0, kIoIn = 1, kIoOut = 2 };
+
 template <typename T, int TC_ = 32, int NT_ = kBlock>
 struct SweepTile {
     static constexpr int TC = TC_;  // columns per workgroup
@@ -54,13 +60,15 @@ struct SweepWaves {
 // keeps x and the face couplings, which neighbouring tiles read again, and
 // x_new, which the next kernel reads.
 template <typename T, int JMAX, int MODE, int TC_ = SweepTile<T>::TC, int NT = kBlock,
-          int CH_ = 0, bool K2 = false, int SC = kSym, bool NTS = false>
+          int CH_ = 0, bool K2 = false, int SC = kSym, bool NTS = false, typename S = T,
+          int IO = kIoNone>
 __global__ void __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(SweepWaves<T, JMAX, MODE, K2, SC>::value)))
 k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
         const T* __restrict__ xc, int nvp_c,
         T* __restrict__ y, T omega, int batch, const int* __restrict__ active, int mid,
-        int rev) {
+        int rev, S* __restrict__ ext) {
+    static_assert(IO != kIoIn || (MODE == kZero && SC == kSym), "the first sweep");
     constexpr int TC = TC_, KG = NT / TC;
     constexpr int BOT = (TC + 63) / 64 * 64;  // first lane of the bottom elimination (own wave)
     static_assert(BOT + TC <= NT, "two elimination lane groups must fit the workgroup");
@@ -87,6 +95,7 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
     y += rhs * nv;
     if (kHasX) x += rhs * nv;
     if (kHasP) xc += rhs * int64_t(nvp_c);
+    if (IO != kIoNone) ext += rhs * (int64_t(nz) * ncol) + c;
     const T* khN = L.kh + nv;
     const int ob = tile_base(c, nz);
 
@@ -149,7 +158,11 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
             for (int d = 0; d < 4; ++d) vsn[jj][d] = T(1);
             if (j < JMAX && k < nz && valid) {
                 const int o = ob + kTile * k;
-                vb[jj] = ld(b + o);
+                if constexpr (IO == kIoIn) {
+                    vb[jj] = T(__builtin_nontemporal_load(ext + int64_t(k) * ncol));
+                } else {
+                    vb[jj] = ld(b + o);
+                }
                 if constexpr (SC != kSym) vs[jj] = L.s[o];
                 vc[jj] = ld(L.cc + o);
                 vm[jj] = ld(L.mm + o);
@@ -209,6 +222,9 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
                          vk[jj][3] * vx[jj][3];
                 }
                 if (K2 && MODE != kZero) r += v2[jj];
+                if constexpr (IO == kIoIn) {
+                    if (valid) const_cast<T*>(b)[ob + kTile * k] = vb[jj];
+                }
                 xo[j] = vx[jj][4];
                 mo[j] = vm[jj];
                 R[k * TC + lc] = r;
@@ -230,7 +246,8 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
             T z = R[k * TC + lc];
             if constexpr (SC == kRowWT) z = z / so[j];
             const T v = (MODE == kZero) ? om * z : om1 * xo[j] + om * z;
-            y[ob + kTile * k] = v;
+            if constexpr (IO == kIoOut) __builtin_nontemporal_store(S(v), ext + int64_t(k) * ncol);
+            else y[ob + kTile * k] = v;
         }
     }
 }
@@ -408,8 +425,11 @@ k_finalize(CgState st, int mode, int cnt, int seq) {
 enum { kDotNone = 0, kDotXY = 1, kDotWY = 2, kDotWYYY = 3 };
 
 // NTS: delta (read once) and y bypass the last-level cache (for levels far
-// larger than it; see k_sweep).
-template <typename T, int DOT, int KC, bool K2 = false, int SC = kSym, bool NTS = false>
+// larger than it; see k_sweep). NAT: x and y in the ABI layout (the apply entry
+// point: a row of 32 or more columns of one level is contiguous there too, and
+// two conversion passes fall away; C192 x 70 253 -> 165 us).
+template <typename T, int DOT, int KC, bool K2 = false, int SC = kSym, bool NTS = false,
+          bool NAT = false>
 __global__ void __launch_bounds__(kBlock)
 k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __restrict__ w,
         int batch, int nkc, CgState st, const int* __restrict__ active, int rev) {
@@ -421,18 +441,19 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
     const int ncol = L.ncol, nz = L.nz;
     const int c = tile * kBlock + threadIdx.x;
     const bool valid = c < ncol;
-    const int64_t nv = L.nvp;
-    x += rhs * nv;
-    y += rhs * nv;
+    const int64_t nv = L.nvp, nx = NAT ? int64_t(nz) * ncol : nv;
+    x += rhs * nx;
+    y += rhs * nx;
     if (DOT >= kDotWY) w += rhs * nv;
     const T* khN = L.kh + nv;
     double acc = 0.0, acc2 = 0.0;
     if (valid) {
         int nb[4];
 #pragma unroll
-        for (int d = 0; d < 4; ++d) nb[d] = tile_base(L.nbr[d * ncol + c], nz);
+        for (int d = 0; d < 4; ++d) nb[d] = NAT ? L.nbr[d * ncol + c] : tile_base(L.nbr[d * ncol + c], nz);
         const uint32_t fW = L.fface[c], fS = L.fface[ncol + c];
         const int ob = tile_base(c, nz);
+        const int xb = NAT ? c : ob, xs = NAT ? ncol : kTile;  // x and y: base, step of a level
         const int k0 = kc * KC;
         // all loads of the chunk are issued before any is used
         T xc[KC + 2], kvv[KC + 1], dl[KC], xn[KC][4], kh[KC][4];
@@ -442,7 +463,7 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
 #pragma unroll
         for (int j = 0; j < KC + 2; ++j) {
             const int k = k0 - 1 + j;
-            xc[j] = (k >= 0 && k < nz) ? x[ob + kTile * k] : T(0);
+            xc[j] = (k >= 0 && k < nz) ? x[xb + xs * k] : T(0);
             sc[j] = T(1);
             if (SC != kSym && k >= 0 && k < nz) sc[j] = L.s[ob + kTile * k];
         }
@@ -455,8 +476,8 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
         // k0-2 .. k0+KC-1
         T xlo = T(0), xhi = T(0), k2v[KC + 2];
         if constexpr (K2) {
-            if (k0 >= 2) xlo = x[ob + kTile * (k0 - 2)];
-            if (k0 + KC + 1 < nz) xhi = x[ob + kTile * (k0 + KC + 1)];
+            if (k0 >= 2) xlo = x[xb + xs * (k0 - 2)];
+            if (k0 + KC + 1 < nz) xhi = x[xb + xs * (k0 + KC + 1)];
 #pragma unroll
             for (int j = 0; j < KC + 2; ++j) {
                 const int k = k0 - 2 + j;
@@ -474,9 +495,9 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
                 if constexpr (NTS) dl[j] = __builtin_nontemporal_load(L.dl + o);
                 else dl[j] = L.dl[o];
 #pragma unroll
-                for (int d = 0; d < 4; ++d) xn[j][d] = x[nb[d] + kTile * k];
+                for (int d = 0; d < 4; ++d) xn[j][d] = x[nb[d] + xs * k];
 #pragma unroll
-                for (int d = 0; d < 4; ++d) sn[j][d] = SC == kRowWT ? L.s[nb[d] + kTile * k] : T(1);
+                for (int d = 0; d < 4; ++d) sn[j][d] = SC == kRowWT ? L.s[(NAT ? tile_base(nb[d], nz) : nb[d]) + kTile * k] : T(1);
                 kh[j][0] = L.kh[o];
                 kh[j][1] = L.kh[fW + uint32_t(kTile * k)];
                 kh[j][2] = khN[o];
@@ -517,8 +538,8 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
                     v += k2v[j + 2] * (xo - xp2);
                     v += k2v[j] * (xo - xm2);
                 }
-                if constexpr (NTS) __builtin_nontemporal_store(v, y + ob + kTile * k);
-                else y[ob + kTile * k] = v;
+                if constexpr (NTS) __builtin_nontemporal_store(v, y + xb + xs * k);
+                else y[xb + xs * k] = v;
                 if (DOT == kDotXY) acc += double(xo) * double(v);
                 if (DOT >= kDotWY) acc += double(w[ob + kTile * k]) * double(v);
                 if (DOT == kDotWYYY) acc2 += double(v) * double(v);
@@ -552,7 +573,7 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
 // 32 x 8 (patches walked column by column: 168 us). y is computed by the same
 // expression as in k_apply and is identical; the partial sums of the dot
 // products follow the patches.
-template <typename T, int DOT, int KC, bool NTS, int PX, bool K2 = false>
+template <typename T, int DOT, int KC, bool NTS, int PX, bool K2 = false, bool NAT = false>
 __global__ void __launch_bounds__(kBlock)
 k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __restrict__ w,
             int batch, int nkc, CgState st, const int* __restrict__ active, int rev) {
@@ -573,24 +594,26 @@ k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T*
     const int c = (pan * N + (q / pwx) * PY + pj) * N + (q % pwx) * PX + pi;
     const bool eW = pi == 0, eE = pi == PX - 1, eS = pj == 0, eN = pj == PY - 1;
     const int ncol = L.ncol, nz = L.nz;
-    const int64_t nv = L.nvp;
-    x += rhs * nv;
-    y += rhs * nv;
+    const int64_t nv = L.nvp, nx = NAT ? int64_t(nz) * ncol : nv;
+    x += rhs * nx;
+    y += rhs * nx;
     if (DOT >= kDotWY) w += rhs * nv;
     const T* khN = L.kh + nv;
     const int ob = tile_base(c, nz);
+    const int xb = NAT ? c : ob, xs = NAT ? ncol : kTile;  // x and y: base, step of a level
+    auto at = [&](int col) { return NAT ? col : tile_base(col, nz); };
     // neighbours in the order of the nbr table (E, W, N, S); only the edge
     // columns look theirs up
     int nb[4] = {0, 0, 0, 0};
     uint32_t fW = 0, fS = 0;
-    if (eE) nb[0] = tile_base(L.nbr[0 * ncol + c], nz);
+    if (eE) nb[0] = at(L.nbr[0 * ncol + c]);
     if (eW) {
-        nb[1] = tile_base(L.nbr[1 * ncol + c], nz);
+        nb[1] = at(L.nbr[1 * ncol + c]);
         fW = L.fface[c];
     }
-    if (eN) nb[2] = tile_base(L.nbr[2 * ncol + c], nz);
+    if (eN) nb[2] = at(L.nbr[2 * ncol + c]);
     if (eS) {
-        nb[3] = tile_base(L.nbr[3 * ncol + c], nz);
+        nb[3] = at(L.nbr[3 * ncol + c]);
         fS = L.fface[ncol + c];
     }
     const bool edge[4] = {eE, eW, eN, eS};
@@ -599,7 +622,7 @@ k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T*
 #pragma unroll
     for (int j = 0; j < KC + 2; ++j) {
         const int k = k0 - 1 + j;
-        xc[j] = (k >= 0 && k < nz) ? x[ob + kTile * k] : T(0);
+        xc[j] = (k >= 0 && k < nz) ? x[xb + xs * k] : T(0);
     }
 #pragma unroll
     for (int j = 0; j < KC + 1; ++j) {
@@ -610,8 +633,8 @@ k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T*
     // k0-2 .. k0+KC-1
     T xlo = T(0), xhi = T(0), k2v[KC + 2];
     if constexpr (K2) {
-        if (k0 >= 2) xlo = x[ob + kTile * (k0 - 2)];
-        if (k0 + KC + 1 < nz) xhi = x[ob + kTile * (k0 + KC + 1)];
+        if (k0 >= 2) xlo = x[xb + xs * (k0 - 2)];
+        if (k0 + KC + 1 < nz) xhi = x[xb + xs * (k0 + KC + 1)];
 #pragma unroll
         for (int j = 0; j < KC + 2; ++j) {
             const int k = k0 - 2 + j;
@@ -632,7 +655,7 @@ k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T*
             kh[j][2] = khN[o];
 #pragma unroll
             for (int d = 0; d < 4; ++d)
-                if (edge[d]) xn[j][d] = x[nb[d] + kTile * k];
+                if (edge[d]) xn[j][d] = x[nb[d] + xs * k];
             if (eW) kh[j][1] = L.kh[fW + uint32_t(kTile * k)];
             if (eS) kh[j][3] = L.kh[fS + uint32_t(kTile * k)];
         }
@@ -674,8 +697,8 @@ k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T*
                 v += k2v[j + 2] * (xo - xp2);
                 v += k2v[j] * (xo - xm2);
             }
-            if constexpr (NTS) __builtin_nontemporal_store(v, y + ob + kTile * k);
-            else y[ob + kTile * k] = v;
+            if constexpr (NTS) __builtin_nontemporal_store(v, y + xb + xs * k);
+            else y[xb + xs * k] = v;
             if (DOT == kDotXY) acc += double(xo) * double(v);
             if (DOT >= kDotWY) acc += double(w[ob + kTile * k]) * double(v);
             if (DOT == kDotWYYY) acc2 += double(v) * double(v);

@@ -47,6 +47,7 @@
 namespace hh {
 
 enum PatchLeg { kDown = 0, kUp = 1, kCoarse = 2 };
+enum PatchLayout { kTiled = 0, kByColumn = 1, kAbi = 2 };
 
 constexpr int kPatchCounts = 8;  // per patch: columns through ring 0, 1, 2, 3; own width
 
@@ -135,7 +136,11 @@ struct PatchArgs {
     T* y;         // the iterate after the leg (kDown: column by column)
     T* bc;        // kDown: the coarse right-hand side
     int nvp_c;
-    int bcol, ccol;  // whether b (and y of kUp, kCoarse) / the coarse vectors are column by column
+    int layout;  // of b (and y of kUp, kCoarse): PatchLayout
+    int ccol;    // whether the coarse vectors are column by column
+    const void* ext_b;  // kAbi: b and the result (float64 values if ext_wide)
+    void* ext_y;
+    int ext_wide;
     T omega;
     int batch;
     const int* active;
@@ -269,6 +274,22 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
     T so[SC != kSym ? JMAX : 1];               // own row weight
     T k2u[K2 ? JMAX : 1], k2d[K2 ? JMAX : 1];  // kv2 at k and k - 2
     constexpr bool HOLD = kPatchHold<T, JMAX, K2>;
+    auto load_b = [&]() {
+        if (A.layout == kAbi && A.ext_wide) {
+            const double* e = static_cast<const double*>(A.ext_b) +
+                              rhs * (int64_t(nz) * A.ncol) + c;
+#pragma unroll
+            for (int j = 0; j < JMAX; ++j) vb[j] = T(e[from(j) * uint32_t(A.ncol)]);
+            return;
+        }
+        const T* e = A.layout == kAbi
+                         ? static_cast<const T*>(A.ext_b) + rhs * (int64_t(nz) * A.ncol) : b;
+        const uint32_t ob = A.layout == kByColumn ? o
+                            : (A.layout == kAbi ? uint32_t(c) : uint32_t(tile_base(c, nz)));
+        const uint32_t sb = A.layout == kByColumn ? 1 : (A.layout == kAbi ? A.ncol : kTile);
+#pragma unroll
+        for (int j = 0; j < JMAX; ++j) vb[j] = load(e, ob + sb * from(j));
+    };
     auto couplings = [&](int i) {  // of places 2 i and 2 i + 1
         pair(kColE, i, vk[2 * i][0], vk[2 * i + 1][0]);
         pair(kColW, i, vk[2 * i][1], vk[2 * i + 1][1]);
@@ -288,8 +309,7 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
     };
     if (lq < nAll) {
         T vc[JMAX];
-        const uint32_t ob = A.bcol ? o : uint32_t(tile_base(c, nz));
-        const uint32_t sb = A.bcol ? 1 : kTile;
+        load_b();
         if constexpr (LEG == kUp) {
             const uint32_t oc = A.ccol ? par * nz : tile_base(par, nz), sc = A.ccol ? 1 : kTile;
             const T* x = A.x + rhs * nv;
@@ -305,7 +325,6 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
         }
 #pragma unroll
         for (int j = 0; j < JMAX; ++j) {
-            vb[j] = load(b, ob + sb * from(j));
             if (j & 1) continue;
             pair(kColC, j >> 1, vc[j], vc[j + 1]);
             pair(kColM, j >> 1, mo[j], mo[j + 1]);
@@ -438,7 +457,7 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
         if (wq < n) run_walk<T, HMAX, false>(R + wb, Cf + wb, top, R[wq * S + HMAX]);
         __syncthreads();
         if (lq < n) {
-            const bool store = it == nsweep - 1 && (LEG == kDown || A.bcol) && lq < cn[0];
+            const bool store = it == nsweep - 1 && (LEG == kDown || A.layout == kByColumn) && lq < cn[0];
             T v[JMAX];
 #pragma unroll
             for (int j = 0; j < JMAX; ++j) v[j] = Rq[patch_place(j)];
@@ -464,11 +483,17 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
         }
     }
     if constexpr (LEG != kDown) {
-        if (A.bcol) return;
+        if (A.layout == kByColumn) return;
         __syncthreads();
+        T* const xt = static_cast<T*>(A.ext_y) + rhs * (int64_t(nz) * A.ncol);
+        double* const xw = static_cast<double*>(A.ext_y) + rhs * (int64_t(nz) * A.ncol);
         for (int e = tid; e < OWN * nz; e += NT) {
             const int q = e % OWN, k = e / OWN;
-            if (q < cn[0]) y[tile_base(cols[q], nz) + kTile * k] = X[q * S + at.of(k)];
+            if (q >= cn[0]) continue;
+            const T v = X[q * S + at.of(k)];
+            if (A.layout == kTiled) y[tile_base(cols[q], nz) + kTile * k] = v;
+            else if (A.ext_wide) xw[k * A.ncol + cols[q]] = double(v);
+            else xt[k * A.ncol + cols[q]] = v;
         }
         return;
     }
@@ -476,12 +501,7 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
     // ---- residual and restriction (k_resid_restrict) -----------------------
     // b of the own columns goes back into R (H holds b / s and reads b again)
     if (lq < cn[0]) {
-        if constexpr (SC == kRowW) {
-            const uint32_t ob = A.bcol ? o : uint32_t(tile_base(c, nz));
-            const uint32_t sb = A.bcol ? 1 : kTile;
-#pragma unroll
-            for (int j = 0; j < JMAX; ++j) vb[j] = load(b, ob + sb * from(j));
-        }
+        if constexpr (SC == kRowW) load_b();
 #pragma unroll
         for (int j = 0; j < JMAX; ++j) Rq[patch_place(j)] = vb[j];
     }
