@@ -178,6 +178,8 @@ struct helmholtz_s {
     // r, p, q, z are tiled [B][nvp]; x and b of the ABI are [B][n]
     double* partial = nullptr;
     double* partial2 = nullptr;
+    double* partial3 = nullptr;
+    double* partial4 = nullptr;
     int pstride = 0;
     double* sc = nullptr;     // [B][8] scalars
     int* active = nullptr;    // [B]
@@ -346,6 +348,8 @@ void layout(helmholtz_s* h, Carver& cv) {
     h->pstride = std::max(std::max(kRedBlocks, ntile0 * nkc0), ntile32);
     h->partial = cv.take<double>(size_t(B) * h->pstride);
     h->partial2 = cv.take<double>(size_t(B) * h->pstride);
+    h->partial3 = cv.take<double>(size_t(B) * h->pstride);
+    h->partial4 = cv.take<double>(size_t(B) * h->pstride);
     h->sc = cv.take<double>(size_t(B) * kScal);
     h->active = cv.take<int>(size_t(B));
     h->upd = cv.take<int>(size_t(B));
@@ -429,8 +433,8 @@ void prof_end(const helmholtz_s* h, int kernel, double bytes, hipStream_t s) {
 }
 
 CgState cg_state(const helmholtz_s* h) {
-    return CgState{h->partial, h->partial2, h->pstride, h->sc, h->active, h->upd,
-                   h->hsc,     h->hact,     h->hseq};
+    return CgState{h->partial, h->partial2, h->partial3, h->partial4, h->pstride, h->sc,
+                   h->active,  h->upd,      h->hsc,      h->hact,     h->hseq};
 }
 
 template <typename T>
@@ -663,8 +667,8 @@ void launch_resid_restrict(const helmholtz_s* h, int l, const T* b, const T* x, 
     }
 }
 
-template <typename T>
-void launch_apply(const helmholtz_s* h, int l, const T* x, T* y, int batch, int dot,
+template <typename T, typename X = T>
+void launch_apply(const helmholtz_s* h, int l, const X* x, T* y, int batch, int dot,
                   const int* active, hipStream_t s, const T* w = nullptr) {
     const Level& v = h->lev[l];
     const int ntile = (v.ncol + kBlock - 1) / kBlock;
@@ -686,9 +690,9 @@ void launch_apply(const helmholtz_s* h, int l, const T* x, T* y, int batch, int 
             constexpr int PX = decltype(px)::value;
             constexpr bool K2 = decltype(k2)::value;
             switch (dot) {
-                case kDotXY: go(k_apply_lds<T, kDotXY, kApplyChunk, NT, PX, K2>); break;
-                case kDotWY: go(k_apply_lds<T, kDotWY, kApplyChunk, NT, PX, K2>); break;
-                default: go(k_apply_lds<T, kDotWYYY, kApplyChunk, NT, PX, K2>); break;
+                case kDotXY: go(k_apply_lds<T, kDotXY, kApplyChunk, NT, PX, K2, false, X>); break;
+                case kDotWY: go(k_apply_lds<T, kDotWY, kApplyChunk, NT, PX, K2, false, X>); break;
+                default: go(k_apply_lds<T, kDotWYYY, kApplyChunk, NT, PX, K2, false, X>); break;
             }
         };
         auto by_width = [&](auto nts, auto k2) {
@@ -704,34 +708,34 @@ void launch_apply(const helmholtz_s* h, int l, const T* x, T* y, int batch, int 
     } else if (h->weighted) {
         if (h->adj) {
             switch (dot) {
-                case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kRowWT>); break;
-                case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kRowWT>); break;
-                default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kRowWT>); break;
+                case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kRowWT, false, false, X>); break;
+                case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kRowWT, false, false, X>); break;
+                default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kRowWT, false, false, X>); break;
             }
         } else {
             switch (dot) {
-                case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kRowW>); break;
-                case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kRowW>); break;
-                default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kRowW>); break;
+                case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kRowW, false, false, X>); break;
+                case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kRowW, false, false, X>); break;
+                default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kRowW, false, false, X>); break;
             }
         }
     } else if (h->nine) {
         switch (dot) {
-            case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, true>); break;
-            case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, true>); break;
-            default: go(k_apply<T, kDotWYYY, kApplyChunk, true>); break;
+            case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, true, kSym, false, false, X>); break;
+            case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, true, kSym, false, false, X>); break;
+            default: go(k_apply<T, kDotWYYY, kApplyChunk, true, kSym, false, false, X>); break;
         }
     } else if (streams_past_cache(h, l, batch, sizeof(T))) {
         switch (dot) {
-            case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kSym, true>); break;
-            case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kSym, true>); break;
-            default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kSym, true>); break;
+            case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kSym, true, false, X>); break;
+            case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kSym, true, false, X>); break;
+            default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kSym, true, false, X>); break;
         }
     } else {
         switch (dot) {
-            case kDotXY: go(k_apply<T, kDotXY, kApplyChunk>); break;
-            case kDotWY: go(k_apply<T, kDotWY, kApplyChunk>); break;
-            default: go(k_apply<T, kDotWYYY, kApplyChunk>); break;
+            case kDotXY: go(k_apply<T, kDotXY, kApplyChunk, false, kSym, false, false, X>); break;
+            case kDotWY: go(k_apply<T, kDotWY, kApplyChunk, false, kSym, false, false, X>); break;
+            default: go(k_apply<T, kDotWYYY, kApplyChunk, false, kSym, false, false, X>); break;
         }
     }
     if (prof)  // x, kh[2], kv, delta (, kv2) read; y written
@@ -960,11 +964,6 @@ int check_batch(const helmholtz_s* h, int32_t batch) {
     return HELMHOLTZ_OK;
 }
 
-template <typename S, typename D>
-void convert(const S* src, D* dst, int64_t n, hipStream_t s) {
-    hipLaunchKernelGGL((k_convert<S, D>), dim3(grid_for(n)), dim3(kBlock), 0, s, src, dst, n);
-}
-
 // Finest-level vector between the ABI layout and the tiled layout, with a cast.
 template <typename S, typename D, bool TO_TILED>
 void retile(const helmholtz_s* h, const S* src, D* dst, int batch, hipStream_t s) {
@@ -1047,25 +1046,30 @@ int wait_published(helmholtz_s* h, hipStream_t s, const std::vector<int>& need, 
     }
 }
 
-// out = M u for float64 tiled vectors (float32 V-cycles convert on the way in
-// and out through the level-0 float32 buffers).
-int precondition_into(helmholtz_s* h, const double* u, double* out, int batch, const int* active,
-                      hipStream_t s) {
-    const bool mixed = h->cfg.mg_precision == HELMHOLTZ_FP32;
-    if (!mixed) {
-        const bool prof = prof_begin(h, HELMHOLTZ_PROF_VCYCLE, s);
-        vcycle_level<double>(h, h->vb64, 0, u, out, batch, active, s);
-        if (prof) prof_end(h, HELMHOLTZ_PROF_VCYCLE, vcycle_bytes(h, batch, 8), s);
-    } else {
-        const VBufs<float>& V = h->vb32;
-        const int64_t n = int64_t(batch) * h->nvp;
-        convert<double, float>(u, V.b[0], n, s);
-        const bool prof = prof_begin(h, HELMHOLTZ_PROF_VCYCLE, s);
-        vcycle_level<float>(h, V, 0, V.b[0], V.x[0], batch, active, s);
-        if (prof) prof_end(h, HELMHOLTZ_PROF_VCYCLE, vcycle_bytes(h, batch, 4), s);
-        convert<float, double>(V.x[0], out, n, s);
-    }
+// out = M u for tiled vectors of the V-cycle's precision.
+template <typename T>
+int precondition_into(helmholtz_s* h, const VBufs<T>& V, const T* u, T* out, int batch,
+                      const int* active, hipStream_t s) {
+    const bool prof = prof_begin(h, HELMHOLTZ_PROF_VCYCLE, s);
+    vcycle_level<T>(h, V, 0, u, out, batch, active, s);
+    if (prof) prof_end(h, HELMHOLTZ_PROF_VCYCLE, vcycle_bytes(h, batch, sizeof(T)), s);
     return last_error();
+}
+
+// Whether the Krylov scalars are formed by the kernels that use them instead of
+// in launches of their own (kMergeMax): few partial sums, and few workgroups
+// that add them up (for C192 x 70 an apply leaves 15552).
+bool scalars_merged(const helmholtz_s* h) {
+    const Level& v = h->lev[0];
+    const int ntile0 = (v.ncol + kBlock - 1) / kBlock;
+    const int nkc0 = (h->nz + kApplyChunk - 1) / kApplyChunk;
+    return ntile0 * nkc0 <= kMergeMax && v.ncolp / kTile <= kMergeMax;
+}
+
+// Workgroups of a vector reduction over the finest level: a few elements per
+// thread, at most kRedBlocks.
+int reduction_blocks(const helmholtz_s* h) {
+    return int(std::min<int64_t>(kRedBlocks, (h->nvp + 4 * kBlock - 1) / (4 * kBlock)));
 }
 
 // Right-preconditioned BiCGStab (Section 4.1) after the shared start
@@ -1073,7 +1077,8 @@ int precondition_into(helmholtz_s* h, const double* u, double* out, int batch, c
 // with H and two V-cycles; the inner products (r0, v), (t, s) with (t, t),
 // and (r0, r) with ||r||^2 are the four global sums of Section 3.7. it/rel
 // are updated for every right-hand side that was active in an iteration.
-int bicgstab_loop(helmholtz_s* h, double* x, int batch, double rtol, int maxiter,
+template <typename Z>
+int bicgstab_loop(helmholtz_s* h, const VBufs<Z>& V, double* x, int batch, double rtol, int maxiter,
                   const std::vector<double>& bnorm2, std::vector<int32_t>& it,
                   std::vector<double>& rel, hipStream_t s) {
     const Level& v0 = h->lev[0];
@@ -1081,8 +1086,21 @@ int bicgstab_loop(helmholtz_s* h, double* x, int batch, double rtol, int maxiter
     const int ntile32 = v0.ncolp / kTile;
     const int ntile0 = (v0.ncol + kBlock - 1) / kBlock;
     const int nkc0 = (h->nz + kApplyChunk - 1) / kApplyChunk;
-    const dim3 red(kRedBlocks * batch), blk(kBlock), fin(kFinBlock), tgrid(ntile32 * batch);
+    const int nred = reduction_blocks(h);
+    const dim3 red(nred * batch), blk(kBlock), fin(kFinBlock), tgrid(ntile32 * batch);
     const CgState st = cg_state(h);
+    const int ndot = ntile0 * nkc0;
+    const int merged = scalars_merged(h) ? ndot : 0;  // partial sums to add where they are used
+    // a float32 V-cycle takes p and s rounded and leaves p_hat and s_hat in
+    // float32 (in the memory of the float64 ones)
+    constexpr bool mixed = sizeof(Z) == 4;
+    float* const u32 = mixed ? h->vb32.b[0] : nullptr;
+    Z* const ph = reinterpret_cast<Z*>(h->z);
+    Z* const shat = reinterpret_cast<Z*>(h->sh);
+    auto precondition_from = [&](const double* u, Z* out) -> int {
+        if constexpr (mixed) return precondition_into<Z>(h, V, u32, out, batch, h->active, s);
+        else return precondition_into<Z>(h, V, u, out, batch, h->active, s);
+    };
     std::vector<int> was_active(batch);
     bool broke = false;
     // Everything of an iteration up to its x and r update skips the
@@ -1093,19 +1111,20 @@ int bicgstab_loop(helmholtz_s* h, double* x, int batch, double rtol, int maxiter
     const bool ahead = !h->prof_on;
     auto first_half = [&](int iter) -> int {
         // p = r + beta (p - omega v); p_hat = M p; v = H p_hat; alpha = rho / (r0, v)
-        hipLaunchKernelGGL(k_bicg_p, red, blk, 0, s, h->r, h->q, h->p, n, kRedBlocks, h->sc,
+        hipLaunchKernelGGL(k_bicg_p, red, blk, 0, s, h->r, h->q, h->p, u32, n, nred, h->sc,
                            h->active, iter == 1 ? 1 : 0);
-        if (int e = precondition_into(h, h->p, h->z, batch, h->active, s)) return e;
-        launch_apply<double>(h, 0, h->z, h->q, batch, kDotWY, h->active, s, h->r0);
-        hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinBiAlpha),
-                           ntile0 * nkc0, 0);
+        if (int e = precondition_from(h->p, ph)) return e;
+        launch_apply<double, Z>(h, 0, ph, h->q, batch, kDotWY, h->active, s, h->r0);
+        if (!merged)
+            hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinBiAlpha), ndot, 0,
+                               0.0);
         // s = r - alpha v; s_hat = M s; t = H s_hat; omega = (t, s) / (t, t)
-        hipLaunchKernelGGL(k_bicg_s, red, blk, 0, s, h->r, h->q, h->s, n, kRedBlocks, h->sc,
-                           h->active);
-        if (int e = precondition_into(h, h->s, h->sh, batch, h->active, s)) return e;
-        launch_apply<double>(h, 0, h->sh, h->t, batch, kDotWYYY, h->active, s, h->s);
-        hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinBiOmega),
-                           ntile0 * nkc0, 0);
+        hipLaunchKernelGGL(k_bicg_s, red, blk, 0, s, h->r, h->q, h->s, u32, n, nred, st, merged);
+        if (int e = precondition_from(h->s, shat)) return e;
+        launch_apply<double, Z>(h, 0, shat, h->t, batch, kDotWYYY, h->active, s, h->s);
+        if (!merged)
+            hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinBiOmega), ndot, 0,
+                               0.0);
         return last_error();
     };
     std::vector<double> fac(batch, 0.05), rel_prev(batch, 1.0);
@@ -1118,9 +1137,10 @@ int bicgstab_loop(helmholtz_s* h, double* x, int batch, double rtol, int maxiter
     for (int iter = 1;; ++iter) {
         for (int i = 0; i < batch; ++i) was_active[i] = h->hact[i];
         // x += alpha p_hat + omega s_hat; r = s - omega t; (r0, r), ||r||^2, published
-        hipLaunchKernelGGL(k_bicg_xr, tgrid, blk, 0, s, x, h->r, h->z, h->sh, h->s, h->t, h->r0,
-                           v0.ncol, h->nz, v0.nvp, st);
-        hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinBiRR), ntile32, iter);
+        hipLaunchKernelGGL((k_bicg_xr<Z>), tgrid, blk, 0, s, x, h->r, ph, shat, h->s, h->t, h->r0,
+                           v0.ncol, h->nz, v0.nvp, st, merged);
+        hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinBiRR), ntile32, iter,
+                           0.0);
         const bool queued = ahead && iter < maxiter && expect_more();
         if (queued)
             if (int e = first_half(iter + 1)) return e;
@@ -1535,24 +1555,22 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     const bool bicg = h->cfg.cg_variant == HELMHOLTZ_BICGSTAB;
     float* r32 = mixed && !bicg ? h->vb32.b[0] : nullptr;
     float* z32 = mixed ? h->vb32.x[0] : nullptr;
-    const dim3 red(kRedBlocks * batch), blk(kBlock), fin(kFinBlock);
+    const int nred = reduction_blocks(h);
+    const dim3 red(nred * batch), blk(kBlock), fin(kFinBlock);
     const CgState st = cg_state(h);
+    const int ndot = ((v0.ncol + kBlock - 1) / kBlock) *
+                     ((h->nz + kApplyChunk - 1) / kApplyChunk);  // partial sums of an apply
+    const bool merged = scalars_merged(h);
+    int rho = kRho;  // where rho stands (alternates if merged)
 
-    // the host mirror doubles as staging for the initial scalars
-    for (int i = 0; i < batch; ++i) {
-        for (int j = 0; j < kScal; ++j) h->hsc[i * kScal + j] = 0.0;
-        h->hsc[i * kScal + kRtol2] = rtol * rtol;
-        __atomic_store_n(&h->hseq[i], -1, __ATOMIC_RELEASE);
-    }
-    HH_CHECK(hipMemcpyAsync(h->sc, h->hsc, size_t(batch) * kScal * sizeof(double),
-                            hipMemcpyHostToDevice, s));
+    for (int i = 0; i < batch; ++i) __atomic_store_n(&h->hseq[i], -1, __ATOMIC_RELEASE);
     // x = 0, r = b, ||b||^2
     // (CG writes x in its first update; the right-hand sides that do not
     // start are zeroed after the norms)
     hipLaunchKernelGGL(k_cg_init, tgrid, blk, 0, s, b, bicg ? x : nullptr, h->r, r32,
                        bicg ? h->r0 : nullptr, v0.ncol, h->nz, v0.nvp, st);
-    hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinBB), ntile32, 0);
-    if (!bicg) hipLaunchKernelGGL(k_cg_zero_idle, tgrid, blk, 0, s, x, v0.ncol, h->nz, st);
+    hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinBB), ntile32, 0,
+                       rtol * rtol);
     if (last_error() != HELMHOLTZ_OK) return HELMHOLTZ_EHIP;
 
     // vectors far larger than the last-level cache: the streams that are not
@@ -1561,7 +1579,7 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     auto dot_rz = [&](const double* q) {
         const int rev = h->flip(0);
         auto go = [&](auto kern, auto z) {
-            hipLaunchKernelGGL(kern, red, blk, 0, s, h->r, z, q, n, kRedBlocks, st, rev);
+            hipLaunchKernelGGL(kern, red, blk, 0, s, h->r, z, q, n, nred, st, rev);
         };
         if (mixed) vnt ? go(k_dot_rz<float, true>, z32) : go(k_dot_rz<float, false>, z32);
         else vnt ? go(k_dot_rz<double, true>, h->z) : go(k_dot_rz<double, false>, h->z);
@@ -1571,7 +1589,8 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
         const int rev = h->flip(0);
         auto go = [&](auto kern, auto z) {
             hipLaunchKernelGGL(kern, tgrid, blk, 0, s, z, h->p, x, v0.ncol, h->nz, v0.nvp, st,
-                               init, xmode, rev);
+                               init, xmode, merged ? nred : 0, rho, int(flex), rev);
+            if (merged) rho = rho == kRho ? int(kRho2) : int(kRho);
         };
         if (mixed) vnt ? go(k_p_update<float, true>, z32) : go(k_p_update<float, false>, z32);
         else vnt ? go(k_p_update<double, true>, h->z) : go(k_p_update<double, false>, h->z);
@@ -1591,7 +1610,8 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     auto cg_start = [&]() -> int {
         if (int e = precondition(h, h->r, h->z, batch, h->active, s, true)) return e;
         dot_rz(nullptr);
-        hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinRho), kRedBlocks, 0);
+        if (!merged)
+            hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinRho), nred, 0, 0.0);
         p_update(1, kXNone);
         return last_error();
     };
@@ -1599,8 +1619,9 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     auto cg_next_m = [&]() -> int {
         if (int e = precondition(h, h->r, h->z, batch, h->active, s, true)) return e;
         dot_rz(flex ? h->q : nullptr);
-        hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st,
-                           int(flex ? kFinBetaFlex : kFinBeta), kRedBlocks, 0);
+        if (!merged)
+            hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st,
+                               int(flex ? kFinBetaFlex : kFinBeta), nred, 0, 0.0);
         return last_error();
     };
 
@@ -1636,11 +1657,19 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
         }
         return status;
     };
-    // x of the idle right-hand sides is cleared after the norms: let it land
+    // x of the right-hand sides that do not start (b = 0 or not finite)
+    bool idle = false;
+    for (int i = 0; i < batch; ++i) idle = idle || !h->hact[i];
+    if (idle && !bicg)
+        hipLaunchKernelGGL(k_cg_zero_idle, tgrid, blk, 0, s, x, v0.ncol, h->nz, st);
     if (!finite || !any) HH_CHECK(hipStreamSynchronize(s));
     if (!finite) return HELMHOLTZ_ENONFINITE;
     if (!any) return finish(HELMHOLTZ_OK);
-    if (bicg) return finish(bicgstab_loop(h, x, batch, rtol, maxiter, bnorm2, it, rel, s));
+    if (bicg)
+        return finish(mixed ? bicgstab_loop<float>(h, h->vb32, x, batch, rtol, maxiter, bnorm2, it,
+                                                   rel, s)
+                            : bicgstab_loop<double>(h, h->vb64, x, batch, rtol, maxiter, bnorm2,
+                                                    it, rel, s));
     if (!ahead)
         if (int e = cg_start()) return e;
 
@@ -1655,8 +1684,6 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
         return false;
     };
 
-    const int ntile0 = (h->lev[0].ncol + kBlock - 1) / kBlock;
-    const int nkc0 = (h->nz + kApplyChunk - 1) / kApplyChunk;
     std::vector<int> was_active(batch);
     int status = HELMHOLTZ_OK;
     for (int iter = 1;; ++iter) {
@@ -1664,19 +1691,21 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
         const bool more = ahead && iter < maxiter && expect_more();
         // q = H p, alpha = rho / p.q
         launch_apply<double>(h, 0, h->p, h->q, batch, kDotXY, h->active, s);
-        hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinAlpha), ntile0 * nkc0,
-                           0);
+        if (!merged)
+            hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinAlpha), ndot, 0,
+                               0.0);
         // r -= alpha q, ||r||^2 and the convergence flags, published; the
         // matching x += alpha p is owed (applied with the next p update, or
         // by x_update where the iteration stops)
         const int rev = h->flip(0);
         if (vnt)
             hipLaunchKernelGGL(k_cg_update<true>, tgrid, blk, 0, s, h->r, r32, h->q, v0.ncol,
-                               h->nz, v0.nvp, st, rev);
+                               h->nz, v0.nvp, st, merged ? ndot : 0, rho, rev);
         else
             hipLaunchKernelGGL(k_cg_update<false>, tgrid, blk, 0, s, h->r, r32, h->q, v0.ncol,
-                               h->nz, v0.nvp, st, rev);
-        hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinRR), ntile32, iter);
+                               h->nz, v0.nvp, st, merged ? ndot : 0, rho, rev);
+        hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinRR), ntile32, iter,
+                           0.0);
         const int xmode = iter == 1 ? kXSet : kXAdd;  // x is first written here
         // queued ahead of the norm: M r of the next iteration, or the x update
         // of the right-hand sides that stop here (no-op for the others)

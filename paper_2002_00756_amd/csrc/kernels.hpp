@@ -277,7 +277,7 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
 // Per right-hand-side scalars sc[rhs*kScal + ...] (kBreak: 1 after a
 // BiCGStab breakdown):
 enum { kBB = 0, kRho = 1, kPQ = 2, kAlpha = 3, kRR = 4, kBeta = 5, kZQ = 6, kRtol2 = 7,
-       kOmega = 8, kBreak = 9, kScal = 12 };
+       kOmega = 8, kBreak = 9, kRho2 = 10, kScal = 12 };
 // CG: BB, then per iteration Rho/Alpha/RR/Beta(Flex). BiCGStab: BB, then per
 // iteration BiAlpha (rho / (r0, v)), BiOmega ((t, s) / (t, t)) and BiRR
 // ((r0, r), ||r||^2, convergence test, beta for the next step).
@@ -287,9 +287,13 @@ enum FinalizeMode { kFinBB = 0, kFinRho = 1, kFinAlpha = 2, kFinRR = 3, kFinBeta
 // Reduction state shared by the Krylov kernels. hsc/hact/hseq live in pinned,
 // host-coherent memory: the finalisation of the norm reductions publishes the
 // scalars there and then the sequence number, which the host polls.
+// partial, partial2 hold the sums of an apply or of k_dot_rz, partial3 and
+// partial4 those of the residual updates, which may still read the former.
 struct CgState {
     double* partial;   // [B][pstride]
     double* partial2;  // [B][pstride]
+    double* partial3;  // [B][pstride]
+    double* partial4;  // [B][pstride]
     int pstride;
     double* sc;        // [B][8]
     int* active;       // [B]
@@ -334,6 +338,15 @@ __device__ __forceinline__ void store_partial(const CgState& st, int rhs, int bl
     }
 }
 
+// The same for the residual updates.
+__device__ __forceinline__ void store_update(const CgState& st, int rhs, int blk, double s1,
+                                             double s2, bool two) {
+    if (threadIdx.x == 0) {
+        st.partial3[int64_t(rhs) * st.pstride + blk] = s1;
+        if (two) st.partial4[int64_t(rhs) * st.pstride + blk] = s2;
+    }
+}
+
 // One block per right-hand side: add the `cnt` partials in a fixed order and
 // derive the Krylov scalar. The norm reductions (kFinBB, kFinRR, kFinBiRR)
 // also publish the scalars and flags to the host mirror, then the sequence
@@ -342,7 +355,7 @@ __device__ __forceinline__ void store_partial(const CgState& st, int rhs, int bl
 constexpr int kFinBlock = 1024;  // threads of the finalisation block
 
 __global__ void __launch_bounds__(kFinBlock)
-k_finalize(CgState st, int mode, int cnt, int seq) {
+k_finalize(CgState st, int mode, int cnt, int seq, double rtol2) {
     __shared__ double sh[kFinBlock / 64];
     const int rhs = blockIdx.x;
     const bool publish = mode == kFinBB || mode == kFinRR || mode == kFinBiRR;
@@ -351,11 +364,17 @@ k_finalize(CgState st, int mode, int cnt, int seq) {
     const bool two = mode == kFinBetaFlex || mode == kFinBiOmega || mode == kFinBiRR;
     double t1 = 0.0, t2 = 0.0;
     if (live) {
-        t1 = reduce_partials(st.partial + int64_t(rhs) * st.pstride, cnt, sh);
-        if (two) t2 = reduce_partials(st.partial2 + int64_t(rhs) * st.pstride, cnt, sh);
+        const bool upd = mode == kFinRR || mode == kFinBiRR;
+        const int64_t at = int64_t(rhs) * st.pstride;
+        t1 = reduce_partials((upd ? st.partial3 : st.partial) + at, cnt, sh);
+        if (two) t2 = reduce_partials((upd ? st.partial4 : st.partial2) + at, cnt, sh);
     }
     if (threadIdx.x != 0) return;
     double* v = st.sc + rhs * kScal;
+    if (mode == kFinBB) {
+        for (int i = 0; i < kScal; ++i) v[i] = 0.0;
+        v[kRtol2] = rtol2;
+    }
     // CG: an x update is owed exactly where r was updated
     if (mode == kFinRR) st.upd[rhs] = live ? 1 : 0;
     switch (live ? mode : -1) {
@@ -420,6 +439,86 @@ k_finalize(CgState st, int mode, int cnt, int seq) {
     }
 }
 
+// The scalars of small problems are formed where they are used: every workgroup
+// of the kernel that needs one adds the partial sums itself (the same order
+// everywhere) and one of them keeps the value. For a few hundred partial sums
+// that costs about 1 us against 3 to 4 for k_finalize in a launch of its own
+// (C12 x 10, float64: solve 335 -> 308 us; C40 x 47, 456 sums: 1097 -> 1086;
+// with C96 x 30's 1728 sums read by 1728 workgroups it costs as much as it
+// saves: forward + backward 2100 -> 2132).
+// rho then alternates between two places, since a workgroup may still read
+// the old one while another writes the new. cnt = 0: the scalars come from
+// k_finalize.
+constexpr int kMergeMax = 512;
+
+__device__ __forceinline__ double cg_alpha(const CgState& st, int rhs, int cnt, int rho,
+                                           bool keep, double* sh) {
+    double* v = st.sc + rhs * kScal;
+    if (!cnt) return v[kAlpha];
+    const double pq = reduce_partials(st.partial + int64_t(rhs) * st.pstride, cnt, sh);
+    const double alpha = v[rho] / pq;
+    if (keep && threadIdx.x == 0) {
+        v[kPQ] = pq;
+        v[kAlpha] = alpha;
+    }
+    return alpha;
+}
+
+// beta of the next direction (flex: Polak-Ribiere, see kFinBetaFlex); first: only
+// rho is kept.
+__device__ __forceinline__ double cg_beta(const CgState& st, int rhs, int cnt, int rho,
+                                          bool flex, bool first, bool keep, double* sh) {
+    double* v = st.sc + rhs * kScal;
+    if (!cnt) return first ? 0.0 : v[kBeta];
+    const int64_t at = int64_t(rhs) * st.pstride;
+    const double rz = reduce_partials(st.partial + at, cnt, sh);
+    double beta = 0.0, zq = 0.0;
+    if (!first && flex) {
+        zq = reduce_partials(st.partial2 + at, cnt, sh);
+        beta = -v[kAlpha] * zq / v[rho];
+    } else if (!first) {
+        beta = rz / v[rho];
+    }
+    if (keep && threadIdx.x == 0) {
+        v[kBeta] = beta;
+        v[kZQ] = zq;
+        v[rho == kRho ? kRho2 : kRho] = rz;
+    }
+    return beta;
+}
+
+// BiCGStab: alpha = rho / (r0, v); zero (r0, v) ends the right-hand side (then
+// ok is false). omega = (t, s) / (t, t).
+__device__ __forceinline__ double bicg_alpha(const CgState& st, int rhs, int cnt, bool keep,
+                                             bool* ok, double* sh) {
+    double* v = st.sc + rhs * kScal;
+    *ok = true;
+    if (!cnt) return v[kAlpha];
+    const double rv = reduce_partials(st.partial + int64_t(rhs) * st.pstride, cnt, sh);
+    *ok = rv != 0.0;
+    const double alpha = *ok ? v[kRho] / rv : 0.0;
+    if (keep && threadIdx.x == 0) {
+        if (*ok) {
+            v[kAlpha] = alpha;
+        } else {
+            v[kBreak] = 1.0;
+            st.active[rhs] = 0;
+        }
+    }
+    return alpha;
+}
+__device__ __forceinline__ double bicg_omega(const CgState& st, int rhs, int cnt, bool keep,
+                                             double* sh) {
+    double* v = st.sc + rhs * kScal;
+    if (!cnt) return v[kOmega];
+    const int64_t at = int64_t(rhs) * st.pstride;
+    const double ts = reduce_partials(st.partial + at, cnt, sh);
+    const double tt = reduce_partials(st.partial2 + at, cnt, sh);
+    const double omega = tt > 0.0 ? ts / tt : 0.0;
+    if (keep && threadIdx.x == 0) v[kOmega] = omega;
+    return omega;
+}
+
 // DOT: 0 none; kDotXY x . y (CG: p . q); kDotWY w . y (BiCGStab: (r0, v));
 // kDotWYYY w . y and y . y (BiCGStab: (t, s), (t, t)). Partial sums per block.
 enum { kDotNone = 0, kDotXY = 1, kDotWY = 2, kDotWYYY = 3 };
@@ -429,9 +528,9 @@ enum { kDotNone = 0, kDotXY = 1, kDotWY = 2, kDotWYYY = 3 };
 // point: a row of 32 or more columns of one level is contiguous there too, and
 // two conversion passes fall away; C192 x 70 253 -> 165 us).
 template <typename T, int DOT, int KC, bool K2 = false, int SC = kSym, bool NTS = false,
-          bool NAT = false>
+          bool NAT = false, typename X = T>
 __global__ void __launch_bounds__(kBlock)
-k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __restrict__ w,
+k_apply(LevelView<T> L, const X* __restrict__ x, T* __restrict__ y, const T* __restrict__ w,
         int batch, int nkc, CgState st, const int* __restrict__ active, int rev) {
     __shared__ double sh[kBlock / 64];
     const int lb = xcd_remap(blockIdx.x, gridDim.x, rev);
@@ -463,7 +562,7 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
 #pragma unroll
         for (int j = 0; j < KC + 2; ++j) {
             const int k = k0 - 1 + j;
-            xc[j] = (k >= 0 && k < nz) ? x[xb + xs * k] : T(0);
+            xc[j] = (k >= 0 && k < nz) ? T(x[xb + xs * k]) : T(0);
             sc[j] = T(1);
             if (SC != kSym && k >= 0 && k < nz) sc[j] = L.s[ob + kTile * k];
         }
@@ -476,8 +575,8 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
         // k0-2 .. k0+KC-1
         T xlo = T(0), xhi = T(0), k2v[KC + 2];
         if constexpr (K2) {
-            if (k0 >= 2) xlo = x[xb + xs * (k0 - 2)];
-            if (k0 + KC + 1 < nz) xhi = x[xb + xs * (k0 + KC + 1)];
+            if (k0 >= 2) xlo = T(x[xb + xs * (k0 - 2)]);
+            if (k0 + KC + 1 < nz) xhi = T(x[xb + xs * (k0 + KC + 1)]);
 #pragma unroll
             for (int j = 0; j < KC + 2; ++j) {
                 const int k = k0 - 2 + j;
@@ -495,7 +594,7 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
                 if constexpr (NTS) dl[j] = __builtin_nontemporal_load(L.dl + o);
                 else dl[j] = L.dl[o];
 #pragma unroll
-                for (int d = 0; d < 4; ++d) xn[j][d] = x[nb[d] + xs * k];
+                for (int d = 0; d < 4; ++d) xn[j][d] = T(x[nb[d] + xs * k]);
 #pragma unroll
                 for (int d = 0; d < 4; ++d) sn[j][d] = SC == kRowWT ? L.s[(NAT ? tile_base(nb[d], nz) : nb[d]) + kTile * k] : T(1);
                 kh[j][0] = L.kh[o];
@@ -573,9 +672,10 @@ k_apply(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __r
 // 32 x 8 (patches walked column by column: 168 us). y is computed by the same
 // expression as in k_apply and is identical; the partial sums of the dot
 // products follow the patches.
-template <typename T, int DOT, int KC, bool NTS, int PX, bool K2 = false, bool NAT = false>
+template <typename T, int DOT, int KC, bool NTS, int PX, bool K2 = false, bool NAT = false,
+          typename X = T>
 __global__ void __launch_bounds__(kBlock)
-k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T* __restrict__ w,
+k_apply_lds(LevelView<T> L, const X* __restrict__ x, T* __restrict__ y, const T* __restrict__ w,
             int batch, int nkc, CgState st, const int* __restrict__ active, int rev) {
     constexpr int PY = kBlock / PX;
     static_assert(PX * PY == kBlock && PX % kTile == 0, "patch rows are whole storage tiles");
@@ -622,7 +722,7 @@ k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T*
 #pragma unroll
     for (int j = 0; j < KC + 2; ++j) {
         const int k = k0 - 1 + j;
-        xc[j] = (k >= 0 && k < nz) ? x[xb + xs * k] : T(0);
+        xc[j] = (k >= 0 && k < nz) ? T(x[xb + xs * k]) : T(0);
     }
 #pragma unroll
     for (int j = 0; j < KC + 1; ++j) {
@@ -633,8 +733,8 @@ k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T*
     // k0-2 .. k0+KC-1
     T xlo = T(0), xhi = T(0), k2v[KC + 2];
     if constexpr (K2) {
-        if (k0 >= 2) xlo = x[xb + xs * (k0 - 2)];
-        if (k0 + KC + 1 < nz) xhi = x[xb + xs * (k0 + KC + 1)];
+        if (k0 >= 2) xlo = T(x[xb + xs * (k0 - 2)]);
+        if (k0 + KC + 1 < nz) xhi = T(x[xb + xs * (k0 + KC + 1)]);
 #pragma unroll
         for (int j = 0; j < KC + 2; ++j) {
             const int k = k0 - 2 + j;
@@ -655,7 +755,7 @@ k_apply_lds(LevelView<T> L, const T* __restrict__ x, T* __restrict__ y, const T*
             kh[j][2] = khN[o];
 #pragma unroll
             for (int d = 0; d < 4; ++d)
-                if (edge[d]) xn[j][d] = x[nb[d] + xs * k];
+                if (edge[d]) xn[j][d] = T(x[nb[d] + xs * k]);
             if (eW) kh[j][1] = L.kh[fW + uint32_t(kTile * k)];
             if (eS) kh[j][3] = L.kh[fS + uint32_t(kTile * k)];
         }
@@ -1296,14 +1396,6 @@ k_coarsen(int ncol_c, int nz, int nvp_f, int nvp_c, const int32_t* __restrict__ 
     }
 }
 
-template <typename S, typename D>
-__global__ void __launch_bounds__(kBlock)
-k_convert(const S* __restrict__ src, D* __restrict__ dst, int64_t n) {
-    for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n;
-         i += int64_t(gridDim.x) * kBlock)
-        dst[i] = D(src[i]);
-}
-
 // ---------------------------------------------------------------------------
 // Krylov (float64) kernels. Reductions are deterministic: a fixed grid of
 // blocks per right-hand side writes one partial sum each, and one block per
@@ -1377,11 +1469,11 @@ k_cg_zero_idle(double* __restrict__ x, int ncol, int nz, CgState st) {
 template <bool NT>
 __global__ void __launch_bounds__(kBlock)
 k_cg_update(double* __restrict__ r, float* __restrict__ r32, const double* __restrict__ q,
-            int ncol, int nz, int nvp, CgState st, int rev) {
+            int ncol, int nz, int nvp, CgState st, int cnt, int rho, int rev) {
     __shared__ double sh[kBlock / 64];
     const TileGrid t = tile_grid(ncol, rev);
     if (!st.active[t.rhs]) return;
-    const double alpha = st.sc[t.rhs * kScal + kAlpha];
+    const double alpha = cg_alpha(st, t.rhs, cnt, rho, t.tile == 0, sh);
     double acc = 0.0;
     if (t.valid) {
         const int64_t it = t.rhs * int64_t(nvp) + tile_base(t.c, nz);
@@ -1394,7 +1486,7 @@ k_cg_update(double* __restrict__ r, float* __restrict__ r32, const double* __res
         }
     }
     const double s = block_sum(acc, sh);
-    store_partial(st, t.rhs, t.tile, s, 0.0, false);
+    store_update(st, t.rhs, t.tile, s, 0.0, false);
 }
 
 // The x update of CG (x in the ABI layout): kXSet x = alpha p (the first
@@ -1477,10 +1569,13 @@ k_dot_rz(const double* __restrict__ r, const Z* __restrict__ z, const double* __
 template <typename Z, bool NT>
 __global__ void __launch_bounds__(kBlock)
 k_p_update(const Z* __restrict__ z, double* __restrict__ p, double* __restrict__ x, int ncol,
-           int nz, int nvp, CgState st, int init, int xmode, int rev) {
+           int nz, int nvp, CgState st, int init, int xmode, int cnt, int rho, int flex,
+           int rev) {
+    __shared__ double sh[kBlock / 64];
     const TileGrid t = tile_grid(ncol, rev);
-    if (!t.valid || !st.active[t.rhs]) return;
-    const double beta = init ? 0.0 : st.sc[t.rhs * kScal + kBeta];
+    if (!st.active[t.rhs]) return;
+    const double beta = cg_beta(st, t.rhs, cnt, rho, flex, init, t.tile == 0, sh);
+    if (!t.valid) return;
     const double alpha = xmode != kXNone ? st.sc[t.rhs * kScal + kAlpha] : 0.0;
     const int64_t ia = t.rhs * int64_t(nz) * ncol + t.c;
     const int64_t it = t.rhs * int64_t(nvp) + tile_base(t.c, nz);
@@ -1557,13 +1652,17 @@ k_face_grad_w(LevelView<double> L, const double* __restrict__ lam, const double*
 }
 
 // ---------------------------------------------------------------------------
-// BiCGStab vector steps (tiled vectors; x in the ABI layout).
+// BiCGStab vector steps (tiled vectors; x in the ABI layout). With a float32
+// V-cycle p and s are rounded for it where they are formed (p32, s32), and its
+// results p_hat, s_hat stay float32: the apply and the x update widen them as
+// they read (conversion passes over all four took 190 of 4680 us in the C96 x 70
+// weighted forward and adjoint solves).
 
 // p = r + beta (p - omega v)   (init: p = r)
 __global__ void __launch_bounds__(kBlock)
 k_bicg_p(const double* __restrict__ r, const double* __restrict__ v, double* __restrict__ p,
-         int64_t n, int nblk, const double* __restrict__ sc, const int* __restrict__ active,
-         int init) {
+         float* __restrict__ p32, int64_t n, int nblk, const double* __restrict__ sc,
+         const int* __restrict__ active, int init) {
     const int rhs = blockIdx.x / nblk, blk = blockIdx.x % nblk;
     if (!active[rhs]) return;
     const double beta = init ? 0.0 : sc[rhs * kScal + kBeta];
@@ -1572,44 +1671,55 @@ k_bicg_p(const double* __restrict__ r, const double* __restrict__ v, double* __r
     grid_range(n, nblk, blk, i0, i1);
     const int64_t off = int64_t(rhs) * n;
 #pragma unroll 4
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += kBlock)
-        p[off + i] = init ? r[off + i] : r[off + i] + beta * (p[off + i] - omega * v[off + i]);
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kBlock) {
+        const double pv =
+            init ? r[off + i] : r[off + i] + beta * (p[off + i] - omega * v[off + i]);
+        p[off + i] = pv;
+        if (p32) p32[off + i] = float(pv);
+    }
 }
 
 // s = r - alpha v
 __global__ void __launch_bounds__(kBlock)
 k_bicg_s(const double* __restrict__ r, const double* __restrict__ v, double* __restrict__ s,
-         int64_t n, int nblk, const double* __restrict__ sc, const int* __restrict__ active) {
+         float* __restrict__ s32, int64_t n, int nblk, CgState st, int cnt) {
+    __shared__ double sh[kBlock / 64];
     const int rhs = blockIdx.x / nblk, blk = blockIdx.x % nblk;
-    if (!active[rhs]) return;
-    const double alpha = sc[rhs * kScal + kAlpha];
+    if (!st.active[rhs]) return;
+    bool ok;
+    const double alpha = bicg_alpha(st, rhs, cnt, blk == 0, &ok, sh);
+    if (!ok) return;
     int64_t i0, i1;
     grid_range(n, nblk, blk, i0, i1);
     const int64_t off = int64_t(rhs) * n;
 #pragma unroll 4
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += kBlock)
-        s[off + i] = r[off + i] - alpha * v[off + i];
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kBlock) {
+        const double sv = r[off + i] - alpha * v[off + i];
+        s[off + i] = sv;
+        if (s32) s32[off + i] = float(sv);
+    }
 }
 
 // x += alpha p_hat + omega s_hat (x in the ABI layout); r = s - omega t;
 // partials (r0, r) and ||r||^2 per tile.
+template <typename Z>
 __global__ void __launch_bounds__(kBlock)
-k_bicg_xr(double* __restrict__ x, double* __restrict__ r, const double* __restrict__ ph,
-          const double* __restrict__ shat, const double* __restrict__ s,
+k_bicg_xr(double* __restrict__ x, double* __restrict__ r, const Z* __restrict__ ph,
+          const Z* __restrict__ shat, const double* __restrict__ s,
           const double* __restrict__ t, const double* __restrict__ r0, int ncol, int nz, int nvp,
-          CgState st) {
+          CgState st, int cnt) {
     __shared__ double sh[kBlock / 64];
     const TileGrid g = tile_grid(ncol);
     if (!st.active[g.rhs]) return;
     const double alpha = st.sc[g.rhs * kScal + kAlpha];
-    const double omega = st.sc[g.rhs * kScal + kOmega];
+    const double omega = bicg_omega(st, g.rhs, cnt, g.tile == 0, sh);
     const int64_t n = int64_t(nz) * ncol;
     double a1 = 0.0, a2 = 0.0;
     if (g.valid) {
         const int64_t ia = g.rhs * n + g.c, it = g.rhs * int64_t(nvp) + tile_base(g.c, nz);
         for (int k = g.g; k < nz; k += kTileGroups) {
             const int64_t o = it + kTile * k;
-            x[ia + int64_t(k) * ncol] += alpha * ph[o] + omega * shat[o];
+            x[ia + int64_t(k) * ncol] += alpha * double(ph[o]) + omega * double(shat[o]);
             const double v = s[o] - omega * t[o];
             r[o] = v;
             a1 += r0[o] * v;
@@ -1619,7 +1729,7 @@ k_bicg_xr(double* __restrict__ x, double* __restrict__ r, const double* __restri
     const double s1 = block_sum(a1, sh);
     __syncthreads();
     const double s2 = block_sum(a2, sh);
-    store_partial(st, g.rhs, g.tile, s1, s2, true);
+    store_update(st, g.rhs, g.tile, s1, s2, true);
 }
 
 // ---------------------------------------------------------------------------
