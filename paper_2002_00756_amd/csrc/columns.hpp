@@ -123,6 +123,11 @@ __device__ __forceinline__ void stream_store(T* p, T v) {
     else *p = v;
 }
 
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) {
+    return __builtin_fma(a, b, c);
+}
+
 // Operator form a kernel is built for: symmetric, row-weighted H = delta + S L,
 // or its transpose H^T = delta + L S.
 enum { kSym = 0, kRowW = 1, kRowWT = 2 };

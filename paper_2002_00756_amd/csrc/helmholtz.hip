@@ -481,7 +481,8 @@ void launch_sweep_b(const helmholtz_s* h, int l, const T* b, const T* x, const T
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(ntile * batch), dim3(kBlock), Tile::lds_bytes(h->nz), s,
                            view<T>(h, l), b, x, xc, nvp_c, y, T(h->cfg.omega), batch, active,
-                           sweep_mid(h->nz), rev, static_cast<T*>(nullptr));
+                           sweep_mid(h->nz), rev, static_cast<T*>(nullptr),
+                           static_cast<double*>(nullptr), 0);
     };
     // only the large levels use 32-column tiles and can stream past the cache
     constexpr bool kCanStream = TC == kTile;
@@ -557,38 +558,38 @@ void launch_sweep_m(const helmholtz_s* h, int l, const T* b, const T* x, const T
 }
 
 // The first (kIoIn, from zero) or the last (kIoOut, plain) sweep of the finest
-// level with b or the result in the ABI layout, S values: 7-point operator, 32-
-// column tiles.
+// level with b or the result in the ABI layout, S values, or the last one with
+// r . z (kIoDot): 7-point operator, 32-column tiles.
 template <typename T, typename S, int JMAX, int MODE, int IO>
 void launch_sweep_io_j(const helmholtz_s* h, const T* b, const T* x, T* y, S* ext, int batch,
-                       hipStream_t s) {
+                       const int* active, hipStream_t s) {
     const Level& v = h->lev[0];
     using Tile = SweepTile<T>;
     const bool prof = MODE == kPlain && prof_begin(h, HELMHOLTZ_PROF_SWEEP_FINE, s);
     const int rev = h->flip(0);
     auto go = [&](auto kern) {
         const T* xc = nullptr;
-        const int* active = nullptr;
         hipLaunchKernelGGL(kern, dim3(v.ncolp / kTile * batch), dim3(kBlock),
                            Tile::lds_bytes(h->nz), s, view<T>(h, 0), b, x, xc, 0, y,
-                           T(h->cfg.omega), batch, active, sweep_mid(h->nz), rev, ext);
+                           T(h->cfg.omega), batch, active, sweep_mid(h->nz), rev, ext,
+                           h->partial, h->pstride);
     };
     if (sweep_streams_past_cache(h, 0, batch, sizeof(T)))
         go(k_sweep<T, JMAX, MODE, kTile, kBlock, 0, false, kSym, true, S, IO>);
     else
         go(k_sweep<T, JMAX, MODE, kTile, kBlock, 0, false, kSym, false, S, IO>);
-    if (prof)
+    if (prof)  // as launch_sweep_b; b or x_new in the ABI layout, or r in place of b
         prof_end(h, HELMHOLTZ_PROF_SWEEP_FINE,
-                 7.0 * sizeof(T) * double(batch) * h->nz * v.ncol, s);
+                 (6.0 * sizeof(T) + sizeof(S)) * double(batch) * h->nz * v.ncol, s);
 }
 
 template <typename T, typename S, int MODE, int IO>
 void launch_sweep_io(const helmholtz_s* h, const T* b, const T* x, T* y, S* ext, int batch,
-                     hipStream_t s) {
+                     const int* active, hipStream_t s) {
     const int jn = (h->nz + 7) / 8;
-    if (jn <= 4) launch_sweep_io_j<T, S, 4, MODE, IO>(h, b, x, y, ext, batch, s);
-    else if (jn <= 9) launch_sweep_io_j<T, S, 9, MODE, IO>(h, b, x, y, ext, batch, s);
-    else launch_sweep_io_j<T, S, 15, MODE, IO>(h, b, x, y, ext, batch, s);
+    if (jn <= 4) launch_sweep_io_j<T, S, 4, MODE, IO>(h, b, x, y, ext, batch, active, s);
+    else if (jn <= 9) launch_sweep_io_j<T, S, 9, MODE, IO>(h, b, x, y, ext, batch, active, s);
+    else launch_sweep_io_j<T, S, 15, MODE, IO>(h, b, x, y, ext, batch, active, s);
 }
 
 // Levels too small to fill the GPU are bound by the latency of a few dependent
@@ -809,11 +810,13 @@ bool on_patches(const helmholtz_s* h, int l) {
 }
 
 // b and x of a V-cycle entry point in the ABI layout; wide: float64 ones of a
-// float32 V-cycle.
+// float32 V-cycle. Or only r: the last sweep takes b from it and leaves the
+// partial sums of r . z, one per tile.
 struct AbiVectors {
     const void* b;
     void* x;
     bool wide;
+    const double* r = nullptr;
 };
 
 // Vectors between two levels on patches are stored column by column: those
@@ -885,22 +888,27 @@ void vcycle_level(helmholtz_s* h, const VBufs<T>& V, int l, const T* b, T* out, 
     // the first sweep from zero and the last plain one, with b and the result in
     // the ABI layout where io is given
     auto sweep_first = [&](T* dst) {
-        if (io && io->wide)
+        if (io && io->b && io->wide)
             launch_sweep_io<T, double, kZero, kIoIn>(
-                h, b, nullptr, dst, static_cast<double*>(const_cast<void*>(io->b)), batch, s);
-        else if (io)
+                h, b, nullptr, dst, static_cast<double*>(const_cast<void*>(io->b)), batch, active,
+                s);
+        else if (io && io->b)
             launch_sweep_io<T, T, kZero, kIoIn>(
-                h, b, nullptr, dst, static_cast<T*>(const_cast<void*>(io->b)), batch, s);
+                h, b, nullptr, dst, static_cast<T*>(const_cast<void*>(io->b)), batch, active, s);
         else
             launch_sweep<T>(h, l, kZero, b, nullptr, nullptr, dst, batch, active, s);
     };
     auto sweep_last = [&](const T* prev, T* dst) {
-        if (io && io->wide)
-            launch_sweep_io<T, double, kPlain, kIoOut>(h, b, prev, dst,
-                                                       static_cast<double*>(io->x), batch, s);
+        if (io && io->r)
+            launch_sweep_io<T, double, kPlain, kIoDot>(h, b, prev, dst,
+                                                       const_cast<double*>(io->r), batch, active,
+                                                       s);
+        else if (io && io->wide)
+            launch_sweep_io<T, double, kPlain, kIoOut>(
+                h, b, prev, dst, static_cast<double*>(io->x), batch, active, s);
         else if (io)
             launch_sweep_io<T, T, kPlain, kIoOut>(h, b, prev, dst, static_cast<T*>(io->x), batch,
-                                                  s);
+                                                  active, s);
         else
             launch_sweep<T>(h, l, kPlain, b, prev, nullptr, dst, batch, active, s);
     };
@@ -950,12 +958,25 @@ void vcycle_level(helmholtz_s* h, const VBufs<T>& V, int l, const T* b, T* out, 
 // patches, or begins with a sweep from zero and ends with a plain one on 32-
 // column tiles (7-point operator; the others keep the passes: two more
 // compiled forms of every sweep).
-template <typename T>
-bool abi_within(const helmholtz_s* h) {
+bool ends_in_plain_sweeps(const helmholtz_s* h) {
     const helmholtz_config& c = h->cfg;
-    if (on_patches<T>(h, 0)) return true;
     if (h->nine || h->weighted || h->lev[0].ncol < kSmallSweepCols) return false;
     return h->L == 1 ? c.n_coarse >= 2 : c.n_pre >= 1 && c.n_post >= 2;
+}
+
+template <typename T>
+bool abi_within(const helmholtz_s* h) {
+    return on_patches<T>(h, 0) || ends_in_plain_sweeps(h);
+}
+
+// Whether the last sweep of a CG preconditioner also forms r . z (kIoDot): as
+// above, where the finest level never runs on patches (with the timing hook on
+// it would run kernel by kernel, and the sums have one order), and the standard
+// beta (the flexible one needs z . q too, of vectors that are in no cache).
+bool dot_within(const helmholtz_s* h) {
+    const bool mixed = h->cfg.mg_precision == HELMHOLTZ_FP32;
+    return h->cfg.cg_variant == HELMHOLTZ_CG_STANDARD && ends_in_plain_sweeps(h) &&
+           !(mixed ? patch_level<float>(h, 0) : patch_level<double>(h, 0));
 }
 
 int check_batch(const helmholtz_s* h, int32_t batch) {
@@ -1002,15 +1023,18 @@ double vcycle_bytes(const helmholtz_s* h, int batch, size_t word) {
 // float32 V-cycle reads r32 (the level-0 float32 right-hand side, which the
 // Krylov kernels keep equal to float(r)) and leaves z32 in the level-0 float32
 // solution buffer; r and z are then not touched. `prof`: time the V-cycle
-// with the kernel timing hook (the solves).
+// with the kernel timing hook (the solves). `dot`: leave the partial sums of
+// r . z (dot_within).
 int precondition(helmholtz_s* h, const double* r, double* z, int batch, const int* active,
-                 hipStream_t s, bool prof = false) {
+                 hipStream_t s, bool prof, bool dot) {
     const bool mixed = h->cfg.mg_precision == HELMHOLTZ_FP32;
     prof = prof && prof_begin(h, HELMHOLTZ_PROF_VCYCLE, s);
+    const AbiVectors with_r{nullptr, nullptr, false, r};
+    const AbiVectors* io = dot ? &with_r : nullptr;
     if (!mixed) {
-        vcycle_level<double>(h, h->vb64, 0, r, z, batch, active, s);
+        vcycle_level<double>(h, h->vb64, 0, r, z, batch, active, s, io);
     } else {
-        vcycle_level<float>(h, h->vb32, 0, h->vb32.b[0], h->vb32.x[0], batch, active, s);
+        vcycle_level<float>(h, h->vb32, 0, h->vb32.b[0], h->vb32.x[0], batch, active, s, io);
     }
     if (prof) prof_end(h, HELMHOLTZ_PROF_VCYCLE, vcycle_bytes(h, batch, mixed ? 4 : 8), s);
     return last_error();
@@ -1555,7 +1579,8 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     const bool bicg = h->cfg.cg_variant == HELMHOLTZ_BICGSTAB;
     float* r32 = mixed && !bicg ? h->vb32.b[0] : nullptr;
     float* z32 = mixed ? h->vb32.x[0] : nullptr;
-    const int nred = reduction_blocks(h);
+    const bool dotted = dot_within(h);
+    const int nred = dotted ? ntile32 : reduction_blocks(h);  // partial sums of r . z
     const dim3 red(nred * batch), blk(kBlock), fin(kFinBlock);
     const CgState st = cg_state(h);
     const int ndot = ((v0.ncol + kBlock - 1) / kBlock) *
@@ -1577,6 +1602,7 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     // read again soon bypass it (see the kernels)
     const bool vnt = streams_past_cache(h, 0, batch, sizeof(double));
     auto dot_rz = [&](const double* q) {
+        if (dotted) return;  // the preconditioner's last sweep has left them
         const int rev = h->flip(0);
         auto go = [&](auto kern, auto z) {
             hipLaunchKernelGGL(kern, red, blk, 0, s, h->r, z, q, n, nred, st, rev);
@@ -1608,7 +1634,7 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     };
     // z = M r, rho = r.z, p = z
     auto cg_start = [&]() -> int {
-        if (int e = precondition(h, h->r, h->z, batch, h->active, s, true)) return e;
+        if (int e = precondition(h, h->r, h->z, batch, h->active, s, true, dotted)) return e;
         dot_rz(nullptr);
         if (!merged)
             hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinRho), nred, 0, 0.0);
@@ -1617,7 +1643,7 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     };
     // z = M r and beta of the next iteration
     auto cg_next_m = [&]() -> int {
-        if (int e = precondition(h, h->r, h->z, batch, h->active, s, true)) return e;
+        if (int e = precondition(h, h->r, h->z, batch, h->active, s, true, dotted)) return e;
         dot_rz(flex ? h->q : nullptr);
         if (!merged)
             hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st,

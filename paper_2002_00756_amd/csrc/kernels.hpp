@@ -36,7 +36,15 @@ enum SweepMode { kZero = 0, kPlain = 1, kProlong = 2, kProlongZero = 3 };
 // kernels that follow; kIoOut: the new iterate goes to ext in the ABI layout
 // instead of y. (A V-cycle entry point then needs no conversion passes: on
 // C192 x 30, float32, 280 -> 267 us.)
-enum { kIoNone = 0, kIoIn = 1, kIoOut = 2 };
+// kIoDot (the last sweep of a CG preconditioner): b is T(ext), ext the float64
+// residual r, tiled, and the partial sums of r . x_new go to part: no pass of its
+// own over r and z (C192 x 70, float32: sweep 85 and pass 35 us -> 105; solve
+// 4146 -> 4118 us, float64 6346 -> 6227; C96 x 30 float64 975 -> 950). r stays in
+// registers through the solve; read a second time instead, from L2, the float64
+// solve took 6268.
+enum { kIoNone = 0, kIoIn = 1, kIoOut = 2, kIoDot = 3 };
+
+__device__ __forceinline__ double block_sum(double v, double* sh);
 
 template <typename T, int TC_ = 32, int NT_ = kBlock>
 struct SweepTile {
@@ -48,11 +56,14 @@ struct SweepTile {
 
 // Waves per SIMD asked of the register allocator: the float32 sweep with
 // prolongation would otherwise take 85 registers and run 5 waves per SIMD;
-// held to 80 it keeps the 6 of the plain sweep (a few values spill).
-template <typename T, int JMAX, int MODE, bool K2, int SC>
+// held to 80 it keeps the 6 of the plain sweep (a few values spill). The
+// sweeps with the product r . x_new likewise (106 and 136; 5 and 4 waves).
+template <typename T, int JMAX, int MODE, bool K2, int SC, int IO>
 struct SweepWaves {
     static constexpr int value =
-        (sizeof(T) == 4 && MODE == kProlong && !K2 && SC == kSym && JMAX <= 9) ? 6 : 1;
+        (sizeof(T) == 4 && MODE == kProlong && !K2 && SC == kSym && JMAX <= 9)
+            ? 6
+            : (IO == kIoDot && JMAX == 9 ? (sizeof(T) == 4 ? 5 : 4) : 1);
 };
 
 // NTS: b and the column factors, read once, are streamed with non-temporal
@@ -63,11 +74,12 @@ template <typename T, int JMAX, int MODE, int TC_ = SweepTile<T>::TC, int NT = k
           int CH_ = 0, bool K2 = false, int SC = kSym, bool NTS = false, typename S = T,
           int IO = kIoNone>
 __global__ void __launch_bounds__(NT)
-__attribute__((amdgpu_waves_per_eu(SweepWaves<T, JMAX, MODE, K2, SC>::value)))
+__attribute__((amdgpu_waves_per_eu(SweepWaves<T, JMAX, MODE, K2, SC, IO>::value)))
 k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
         const T* __restrict__ xc, int nvp_c,
         T* __restrict__ y, T omega, int batch, const int* __restrict__ active, int mid,
-        int rev, S* __restrict__ ext) {
+        int rev, S* __restrict__ ext, double* __restrict__ part, int pstride) {
+    static_assert(IO != kIoDot || (MODE == kPlain && SC == kSym && !K2), "the last sweep");
     static_assert(IO != kIoIn || (MODE == kZero && SC == kSym), "the first sweep");
     constexpr int TC = TC_, KG = NT / TC;
     constexpr int BOT = (TC + 63) / 64 * 64;  // first lane of the bottom elimination (own wave)
@@ -95,7 +107,8 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
     y += rhs * nv;
     if (kHasX) x += rhs * nv;
     if (kHasP) xc += rhs * int64_t(nvp_c);
-    if (IO != kIoNone) ext += rhs * (int64_t(nz) * ncol) + c;
+    if (IO == kIoDot) ext += rhs * nv;
+    else if (IO != kIoNone) ext += rhs * (int64_t(nz) * ncol) + c;
     const T* khN = L.kh + nv;
     const int ob = tile_base(c, nz);
 
@@ -122,7 +135,7 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
             nOut = (((c / L.N) % L.N) & 1) != 0;
         }
     }
-    auto ld = [](const T* p) -> T {
+    auto ld = [](const auto* p) {
         if constexpr (NTS) return __builtin_nontemporal_load(p);
         else return *p;
     };
@@ -138,6 +151,7 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
     constexpr int CH = CH_ > 0 ? CH_ : (MODE == kZero ? 8 : 2);
     T xo[JMAX], mo[JMAX];
     T so[SC == kRowWT ? JMAX : 1];  // H^T: own weight, for z / s
+    S ro[IO == kIoDot ? JMAX : 1];  // r
 #pragma unroll
     for (int j0 = 0; j0 < JMAX; j0 += CH) {
         T vb[CH], vc[CH], vm[CH], vx[CH][5], vk[CH][4];
@@ -160,6 +174,9 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
                 const int o = ob + kTile * k;
                 if constexpr (IO == kIoIn) {
                     vb[jj] = T(__builtin_nontemporal_load(ext + int64_t(k) * ncol));
+                } else if constexpr (IO == kIoDot) {
+                    ro[j] = ld(ext + o);
+                    vb[jj] = T(ro[j]);
                 } else {
                     vb[jj] = ld(b + o);
                 }
@@ -237,7 +254,8 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
     column_solve<T, JMAX>(R, Cf, E1, E2, mo, tid, lc, kg, KG, BOT, mid, nz, TC, TC);
 
     // ---- phase 5: relaxation and store -------------------------------------
-    if (!valid) return;
+    if (IO != kIoDot && !valid) return;
+    double acc = 0.0;
     const T om = omega, om1 = T(1) - omega;
 #pragma unroll
     for (int j = 0; j < JMAX; ++j) {
@@ -245,10 +263,18 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
         if (k < nz) {
             T z = R[k * TC + lc];
             if constexpr (SC == kRowWT) z = z / so[j];
-            const T v = (MODE == kZero) ? om * z : om1 * xo[j] + om * z;
+            // (kIoDot: the rounding that the compiler chooses for the plain sweep)
+            const T v = (MODE == kZero)  ? om * z
+                        : (IO == kIoDot) ? fused(om1, xo[j], om * z)
+                                         : om1 * xo[j] + om * z;
             if constexpr (IO == kIoOut) __builtin_nontemporal_store(S(v), ext + int64_t(k) * ncol);
-            else y[ob + kTile * k] = v;
+            else if (IO != kIoDot || valid) y[ob + kTile * k] = v;
+            if constexpr (IO == kIoDot) acc += valid ? double(ro[j]) * double(v) : 0.0;
         }
+    }
+    if constexpr (IO == kIoDot) {
+        const double sum = block_sum(acc, reinterpret_cast<double*>(smem_raw));
+        if (tid == 0) part[int64_t(rhs) * pstride + tile] = sum;
     }
 }
 

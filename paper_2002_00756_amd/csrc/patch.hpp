@@ -149,11 +149,6 @@ struct PatchArgs {
     int rev;
 };
 
-__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fused(double a, double b, double c) {
-    return __builtin_fma(a, b, c);
-}
-
 // One lane's walk over half a column (the recurrences of walk in columns.hpp):
 // HMAX rows from r and c on, upwards (ELIM: t_i = r_i + c_{i-1} t_{i-1}; returns
 // c_last t_last, what row mid takes) or downwards (z_i = r_i + c_i z_{i+1}, with
