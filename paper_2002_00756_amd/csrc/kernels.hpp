@@ -335,20 +335,25 @@ __device__ __forceinline__ void grid_range(int64_t n, int nblk, int blk, int64_t
     i1 = min(n, i0 + per);
 }
 
-// Sum `cnt` partials in a fixed order (result in every thread). Four
-// independent accumulators per thread keep several loads in flight.
-__device__ __forceinline__ double reduce_partials(const double* part, int cnt, double* sh) {
-    const int step = blockDim.x;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int i = threadIdx.x;
-    for (; i + 3 * step < cnt; i += 4 * step) {
-        a0 += part[i];
-        a1 += part[i + step];
-        a2 += part[i + 2 * step];
-        a3 += part[i + 3 * step];
+// This thread's share of `cnt` (> 0) partials, in a fixed order. The loads of a
+// batch do not depend on the count (places past the end read the last one), so
+// that they are all in flight together.
+template <int NT, int U>
+__device__ __forceinline__ double thread_partials(const double* part, int cnt) {
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int base = threadIdx.x; base < cnt; base += U * NT) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = part[min(base + u * NT, cnt - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u & 3] += base + u * NT < cnt ? v[u] : 0.0;
     }
-    for (; i < cnt; i += step) a0 += part[i];
-    const double s = block_sum((a0 + a1) + (a2 + a3), sh);
+    return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// Sum `cnt` partials in a fixed order (256 threads; result in every one).
+__device__ __forceinline__ double reduce_partials(const double* part, int cnt, double* sh) {
+    const double s = block_sum(thread_partials<kBlock, 2>(part, cnt), sh);
     __syncthreads();
     if (threadIdx.x == 0) sh[0] = s;
     __syncthreads();
@@ -378,89 +383,121 @@ __device__ __forceinline__ void store_update(const CgState& st, int rhs, int blk
 // also publish the scalars and flags to the host mirror, then the sequence
 // number `seq`; they publish even for a right-hand side that is no longer
 // active (its values unchanged), so the host never waits in vain.
+// Bound by the latency of its dependent steps: the partials, the old scalars and
+// the flag are read at once, and what is published is taken from registers.
+// (With the partials in a loop of one load each, the scalars after them and the
+// published ones read back it took 5.7 us for 1728 sums and 6.7 for 15552, now
+// 4.4 and 5.4. Solves: C12 x 10 305 -> 294 us, C40 x 47 1091 -> 1068, C96 x 30
+// 946 -> 935, C192 x 70 4106 -> 4089.)
 constexpr int kFinBlock = 1024;  // threads of the finalisation block
 
 __global__ void __launch_bounds__(kFinBlock)
 k_finalize(CgState st, int mode, int cnt, int seq, double rtol2) {
-    __shared__ double sh[kFinBlock / 64];
+    constexpr int NW = kFinBlock / 64;
+    __shared__ double sh[2][NW];
     const int rhs = blockIdx.x;
     const bool publish = mode == kFinBB || mode == kFinRR || mode == kFinBiRR;
-    const bool live = mode == kFinBB || st.active[rhs] != 0;
-    if (!live && !publish) return;
     const bool two = mode == kFinBetaFlex || mode == kFinBiOmega || mode == kFinBiRR;
-    double t1 = 0.0, t2 = 0.0;
-    if (live) {
-        const bool upd = mode == kFinRR || mode == kFinBiRR;
-        const int64_t at = int64_t(rhs) * st.pstride;
-        t1 = reduce_partials((upd ? st.partial3 : st.partial) + at, cnt, sh);
-        if (two) t2 = reduce_partials((upd ? st.partial4 : st.partial2) + at, cnt, sh);
-    }
-    if (threadIdx.x != 0) return;
+    const bool upd = mode == kFinRR || mode == kFinBiRR;
+    const int64_t at = int64_t(rhs) * st.pstride;
+    int active = st.active[rhs];
     double* v = st.sc + rhs * kScal;
+    double c[kScal];
+#pragma unroll
+    for (int i = 0; i < kScal; ++i) c[i] = v[i];
+    double a1 = thread_partials<kFinBlock, 8>((upd ? st.partial3 : st.partial) + at, cnt);
+    double a2 = 0.0;
+    if (two) a2 = thread_partials<kFinBlock, 8>((upd ? st.partial4 : st.partial2) + at, cnt);
+    const bool live = mode == kFinBB || active != 0;
+    if (!live && !publish) return;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a1 += __shfl_xor(a1, o, 64);
+        a2 += __shfl_xor(a2, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][threadIdx.x >> 6] = a1;
+        sh[1][threadIdx.x >> 6] = a2;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double t1 = 0.0, t2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        t1 += sh[0][i];
+        t2 += sh[1][i];
+    }
     if (mode == kFinBB) {
-        for (int i = 0; i < kScal; ++i) v[i] = 0.0;
-        v[kRtol2] = rtol2;
+#pragma unroll
+        for (int i = 0; i < kScal; ++i) c[i] = 0.0;
+        c[kRtol2] = rtol2;
     }
     // CG: an x update is owed exactly where r was updated
     if (mode == kFinRR) st.upd[rhs] = live ? 1 : 0;
     switch (live ? mode : -1) {
         case kFinBB:
-            v[kBB] = t1;
-            v[kRR] = t1;
-            v[kRho] = t1;  // BiCGStab: (r0, r) with r0 = r = b
-            st.active[rhs] = (t1 > 0.0) ? 1 : 0;
+            c[kBB] = t1;
+            c[kRR] = t1;
+            c[kRho] = t1;  // BiCGStab: (r0, r) with r0 = r = b
+            active = (t1 > 0.0) ? 1 : 0;
             break;
         case kFinRho:
-            v[kRho] = t1;
+            c[kRho] = t1;
             break;
         case kFinAlpha:
-            v[kPQ] = t1;
-            v[kAlpha] = v[kRho] / t1;
+            c[kPQ] = t1;
+            c[kAlpha] = c[kRho] / t1;
             break;
         case kFinRR:
-            v[kRR] = t1;
-            if (t1 <= v[kRtol2] * v[kBB]) st.active[rhs] = 0;
+            c[kRR] = t1;
+            if (t1 <= c[kRtol2] * c[kBB]) active = 0;
             break;
         case kFinBeta:
-            v[kBeta] = t1 / v[kRho];
-            v[kRho] = t1;
+            c[kBeta] = t1 / c[kRho];
+            c[kRho] = t1;
             break;
         case kFinBetaFlex:
             // Polak-Ribiere: z.(r_new - r_old) / rho with r_new - r_old = -alpha q
-            v[kBeta] = -v[kAlpha] * t2 / v[kRho];
-            v[kZQ] = t2;
-            v[kRho] = t1;
+            c[kBeta] = -c[kAlpha] * t2 / c[kRho];
+            c[kZQ] = t2;
+            c[kRho] = t1;
             break;
         case kFinBiAlpha:  // t1 = (r0, v)
             if (t1 == 0.0) {
-                v[kBreak] = 1.0;
-                st.active[rhs] = 0;
+                c[kBreak] = 1.0;
+                active = 0;
             } else {
-                v[kAlpha] = v[kRho] / t1;
+                c[kAlpha] = c[kRho] / t1;
             }
             break;
         case kFinBiOmega:  // t1 = (t, s), t2 = (t, t); t = 0 only if s = 0
-            v[kOmega] = t2 > 0.0 ? t1 / t2 : 0.0;
+            c[kOmega] = t2 > 0.0 ? t1 / t2 : 0.0;
             break;
         case kFinBiRR:  // t1 = (r0, r), t2 = ||r||^2
-            v[kRR] = t2;
-            if (t2 <= v[kRtol2] * v[kBB]) {
-                st.active[rhs] = 0;
-            } else if (t1 == 0.0 || v[kOmega] == 0.0) {
-                v[kBreak] = 1.0;
-                st.active[rhs] = 0;
+            c[kRR] = t2;
+            if (t2 <= c[kRtol2] * c[kBB]) {
+                active = 0;
+            } else if (t1 == 0.0 || c[kOmega] == 0.0) {
+                c[kBreak] = 1.0;
+                active = 0;
             } else {
-                v[kBeta] = (t1 / v[kRho]) * (v[kAlpha] / v[kOmega]);
-                v[kRho] = t1;
+                c[kBeta] = (t1 / c[kRho]) * (c[kAlpha] / c[kOmega]);
+                c[kRho] = t1;
             }
             break;
         default:
             break;
     }
+    if (live) {
+        st.active[rhs] = active;
+#pragma unroll
+        for (int i = 0; i < kScal; ++i) v[i] = c[i];
+    }
     if (publish) {
-        for (int i = 0; i < kScal; ++i) st.hsc[rhs * kScal + i] = v[i];
-        st.hact[rhs] = st.active[rhs];
-        __threadfence_system();
+#pragma unroll
+        for (int i = 0; i < kScal; ++i) st.hsc[rhs * kScal + i] = c[i];
+        st.hact[rhs] = active;
+        // (the release orders the stores above before it)
         __hip_atomic_store(&st.hseq[rhs], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
@@ -468,7 +505,7 @@ k_finalize(CgState st, int mode, int cnt, int seq, double rtol2) {
 // The scalars of small problems are formed where they are used: every workgroup
 // of the kernel that needs one adds the partial sums itself (the same order
 // everywhere) and one of them keeps the value. For a few hundred partial sums
-// that costs about 1 us against 3 to 4 for k_finalize in a launch of its own
+// that costs under 1 us against 3 to 4 for k_finalize in a launch of its own
 // (C12 x 10, float64: solve 335 -> 308 us; C40 x 47, 456 sums: 1097 -> 1086;
 // with C96 x 30's 1728 sums read by 1728 workgroups it costs as much as it
 // saves: forward + backward 2100 -> 2132).
@@ -481,8 +518,9 @@ __device__ __forceinline__ double cg_alpha(const CgState& st, int rhs, int cnt, 
                                            bool keep, double* sh) {
     double* v = st.sc + rhs * kScal;
     if (!cnt) return v[kAlpha];
+    const double old = v[rho];
     const double pq = reduce_partials(st.partial + int64_t(rhs) * st.pstride, cnt, sh);
-    const double alpha = v[rho] / pq;
+    const double alpha = old / pq;
     if (keep && threadIdx.x == 0) {
         v[kPQ] = pq;
         v[kAlpha] = alpha;
@@ -497,13 +535,14 @@ __device__ __forceinline__ double cg_beta(const CgState& st, int rhs, int cnt, i
     double* v = st.sc + rhs * kScal;
     if (!cnt) return first ? 0.0 : v[kBeta];
     const int64_t at = int64_t(rhs) * st.pstride;
+    const double old = v[rho], alpha = v[kAlpha];
     const double rz = reduce_partials(st.partial + at, cnt, sh);
     double beta = 0.0, zq = 0.0;
     if (!first && flex) {
         zq = reduce_partials(st.partial2 + at, cnt, sh);
-        beta = -v[kAlpha] * zq / v[rho];
+        beta = -alpha * zq / old;
     } else if (!first) {
-        beta = rz / v[rho];
+        beta = rz / old;
     }
     if (keep && threadIdx.x == 0) {
         v[kBeta] = beta;
@@ -520,9 +559,10 @@ __device__ __forceinline__ double bicg_alpha(const CgState& st, int rhs, int cnt
     double* v = st.sc + rhs * kScal;
     *ok = true;
     if (!cnt) return v[kAlpha];
+    const double rho = v[kRho];
     const double rv = reduce_partials(st.partial + int64_t(rhs) * st.pstride, cnt, sh);
     *ok = rv != 0.0;
-    const double alpha = *ok ? v[kRho] / rv : 0.0;
+    const double alpha = *ok ? rho / rv : 0.0;
     if (keep && threadIdx.x == 0) {
         if (*ok) {
             v[kAlpha] = alpha;
