@@ -242,20 +242,27 @@ int patch_kind(const helmholtz_config* c, int N, bool coarsest) {
 // Whether a patch of this size pays on columns of nz levels: the deeper ones
 // need more registers than a workgroup of that size has (the values spill:
 // coarsest level C24 x 70 52 / 36 us), or the level's traffic, multiplied by
-// the rings, outgrows what the launches cost: with 8 x 4 patches vectors of up
-// to 3 MB gain (C48 x 47 float32, 2.6 MB, 81 / 85 us; C64 x 30, 2.9 MB, 74 / 80;
-// C48 x 70, 3.9 MB, 108 / 106).
+// the rings, outgrows what the launches cost. On patches the columns have
+// `places` rows, pads included (32 at least, 64 with the 9-cell and the weighted
+// operators), so with 8 x 4 patches it is the padded vector that counts: up to
+// 2.5 MiB they gain (two levels, on patches / kernel by kernel: C40 x 2 9-cell
+// float32, 2.3 MiB, 35 / 41 us; C54 x 6 float32, 2.1 MiB, 32 / 46; but C54 x 6
+// 9-cell float32, 4.3 MiB, 53 / 48, C42 x 2 twice, weighted float64, 10 MiB, 86 /
+// 44), and to 3.5 where three fifths of the places are levels (C64 x 20 float32,
+// 3.0 MiB, 45 / 50; C48 x 47, 3.4 MiB, 81 / 85; C48 x 70, 5.1 MiB, 108 / 106).
 template <typename T>
-bool patch_pays(int kind, int nz, int64_t vector_values, bool nine) {
+bool patch_pays(int kind, int nz, int places, int64_t columns, bool nine) {
     constexpr bool f32 = sizeof(T) == 4;
     switch (kind) {
         case 0:
         case 2: return !nine || nz <= (f32 ? 80 : 48);
         case 1: return nz <= (nine ? (f32 ? 80 : 48) : (f32 ? HELMHOLTZ_NZ_MAX : 80));
         case 3: return nz <= (nine ? 32 : (f32 ? 64 : 48));
-        default:
-            return vector_values * int64_t(sizeof(T)) <= (int64_t(3) << 20) &&
+        default: {
+            const int64_t kib = columns * places * int64_t(sizeof(T)) >> 10;
+            return kib <= (5 * nz >= 3 * places ? 3584 : 2560) &&
                    nz <= (nine ? (f32 ? 48 : 32) : (f32 ? 80 : 64));
+        }
     }
 }
 
@@ -266,7 +273,7 @@ bool patch_level(const helmholtz_s* h, int l) {
     const Level& v = h->lev[l];
     if (v.patch < 0 || (sizeof(T) == 8 && h->cfg.mg_precision == HELMHOLTZ_FP32)) return false;
     const int jmax = patch_levels(h->nz, !h->nine && !h->weighted);
-    return patch_pays<T>(v.patch, h->nz, int64_t(v.nvp) * h->B, h->nine) &&
+    return patch_pays<T>(v.patch, h->nz, kPatchLanes * jmax, int64_t(v.ncol) * h->B, h->nine) &&
            patch_lds_bytes<T>(kPatchShapes[v.patch].ncp, jmax) <= kLdsBytes;
 }
 
