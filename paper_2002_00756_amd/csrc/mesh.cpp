@@ -125,7 +125,7 @@ void build_patches(int N, const int32_t* nbr, int pw, int ph, int depth, int ncp
     std::fill(lnbs, lnbs + np * ncp, 0u);
     std::fill(cnts, cnts + np * 8, 0);
     std::vector<int32_t> place(ncol, -1);  // column -> place in the current list
-    size_t p = 0;
+    size_t p = 0, like = np;
     for (int pan = 0; pan < 6; ++pan)
         for (int j0 = 0; j0 < N; j0 += ph)
             for (int i0 = 0; i0 < N; i0 += pw, ++p) {
@@ -133,6 +133,18 @@ void build_patches(int N, const int32_t* nbr, int pw, int ph, int depth, int ncp
                 int32_t* col = cols + p * ncp;
                 int32_t* cnt = cnts + p * 8;
                 uint32_t* lnb = lnbs + p * ncp;
+                // a patch whose rings stay inside its panel is a shifted copy of
+                // the first such one
+                const bool inner = i0 >= depth && i0 + pw + depth <= N && j0 >= depth &&
+                                   j0 + ph + depth <= N;
+                if (inner && like < np) {
+                    const int32_t by = int32_t((int64_t(pan) * N + j0) * N + i0) - cols[like * ncp];
+                    for (int q = 0; q < ncp; ++q) col[q] = cols[like * ncp + q] + by;
+                    std::copy_n(cnts + like * 8, 8, cnt);
+                    std::copy_n(lnbs + like * ncp, ncp, lnb);
+                    continue;
+                }
+                if (inner) like = p;
                 int n = 0;
                 auto add = [&](int32_t c) {
                     if (place[c] < 0) {
