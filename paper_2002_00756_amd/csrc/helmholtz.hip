@@ -585,9 +585,9 @@ void launch_sweep_io_j(const helmholtz_s* h, const T* b, const T* x, T* y, S* ex
         go(k_sweep<T, JMAX, MODE, kTile, kBlock, 0, false, kSym, true, S, IO>);
     else
         go(k_sweep<T, JMAX, MODE, kTile, kBlock, 0, false, kSym, false, S, IO>);
-    if (prof)  // as launch_sweep_b; b or x_new in the ABI layout, or r in place of b
+    if (prof)
         prof_end(h, HELMHOLTZ_PROF_SWEEP_FINE,
-                 (6.0 * sizeof(T) + sizeof(S)) * double(batch) * h->nz * v.ncol, s);
+                 7.0 * sizeof(T) * double(batch) * h->nz * v.ncol, s);
 }
 
 template <typename T, typename S, int MODE, int IO>
@@ -1609,7 +1609,16 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     // read again soon bypass it (see the kernels)
     const bool vnt = streams_past_cache(h, 0, batch, sizeof(double));
     auto dot_rz = [&](const double* q) {
-        if (dotted) return;  // the preconditioner's last sweep has left them
+        if (dotted) {
+            if (!h->prof_on) return;  // the preconditioner's last sweep has left them
+            if (mixed)
+                hipLaunchKernelGGL(k_dot_tiles<float>, tgrid, blk, 0, s, h->r, z32, v0.ncol,
+                                   h->nz, v0.nvp, st);
+            else
+                hipLaunchKernelGGL(k_dot_tiles<double>, tgrid, blk, 0, s, h->r, h->z, v0.ncol,
+                                   h->nz, v0.nvp, st);
+            return;
+        }
         const int rev = h->flip(0);
         auto go = [&](auto kern, auto z) {
             hipLaunchKernelGGL(kern, red, blk, 0, s, h->r, z, q, n, nred, st, rev);
@@ -1641,7 +1650,7 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     };
     // z = M r, rho = r.z, p = z
     auto cg_start = [&]() -> int {
-        if (int e = precondition(h, h->r, h->z, batch, h->active, s, true, dotted)) return e;
+        if (int e = precondition(h, h->r, h->z, batch, h->active, s, true, dotted && !h->prof_on)) return e;
         dot_rz(nullptr);
         if (!merged)
             hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st, int(kFinRho), nred, 0, 0.0);
@@ -1650,7 +1659,7 @@ int helmholtz_solve(helmholtz_t h, const double* b, double* x, int32_t batch, do
     };
     // z = M r and beta of the next iteration
     auto cg_next_m = [&]() -> int {
-        if (int e = precondition(h, h->r, h->z, batch, h->active, s, true, dotted)) return e;
+        if (int e = precondition(h, h->r, h->z, batch, h->active, s, true, dotted && !h->prof_on)) return e;
         dot_rz(flex ? h->q : nullptr);
         if (!merged)
             hipLaunchKernelGGL(k_finalize, dim3(batch), fin, 0, s, st,

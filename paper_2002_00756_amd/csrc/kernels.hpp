@@ -269,7 +269,9 @@ k_sweep(LevelView<T> L, const T* __restrict__ b, const T* __restrict__ x,
                                          : om1 * xo[j] + om * z;
             if constexpr (IO == kIoOut) __builtin_nontemporal_store(S(v), ext + int64_t(k) * ncol);
             else if (IO != kIoDot || valid) y[ob + kTile * k] = v;
-            if constexpr (IO == kIoDot) acc += valid ? double(ro[j]) * double(v) : 0.0;
+            if constexpr (IO == kIoDot) {
+                if (valid) acc = fused(double(ro[j]), double(v), acc);
+            }
         }
     }
     if constexpr (IO == kIoDot) {
@@ -1625,6 +1627,24 @@ k_dot_rz(const double* __restrict__ r, const Z* __restrict__ z, const double* __
         s2 = block_sum(a2, sh);
     }
     store_partial(st, rhs, blk, s1, s2, q != nullptr);
+}
+
+// The partial sums that the sweep with r . z (kIoDot) leaves, the same bits: with
+// the timing hook on, which times plain sweeps, it runs as one and this follows.
+template <typename Z>
+__global__ void __launch_bounds__(kBlock)
+k_dot_tiles(const double* __restrict__ r, const Z* __restrict__ z, int ncol, int nz, int nvp,
+            CgState st) {
+    __shared__ double sh[kBlock / 64];
+    const TileGrid t = tile_grid(ncol);
+    if (!st.active[t.rhs]) return;
+    const int64_t it = t.rhs * int64_t(nvp) + tile_base(t.c, nz);
+    double acc = 0.0;
+    if (t.valid)
+        for (int k = t.g; k < nz; k += kTileGroups)
+            acc = fused(r[it + kTile * k], double(z[it + kTile * k]), acc);
+    const double s = block_sum(acc, sh);
+    store_partial(st, t.rhs, t.tile, s, 0.0, false);
 }
 
 // p = z + beta p (init: p = z) for the right-hand sides still iterating and,

@@ -52,3 +52,22 @@ def test_three_iterations(N, nz, L, max_batch, precision, tol):
     got = op.solve(one, rtol=0.0, maxiter=3)
     assert got.iters == [0, 3] and not bool(got.x[0].any())
     assert float(norm(got.x - x)[1]) <= tol * float(norm(x)[1])
+
+
+@pytest.mark.parametrize("precision,word", [("fp64", 8), ("fp32", 4)])
+def test_timing_hook_sees_plain_sweeps(precision, word):
+    """With the hook on the last sweep runs as a plain one, 7 words per unknown,
+    and r . z follows it: the counts of the hook, and the same bits."""
+    from paper_2002_00756_amd import Operator, _lib
+    print(f"dot sweep, hook on, {precision}", flush=True)
+    N, nz = 30, 33
+    kh, kv, delta = workloads.coefficients(N, nz, 1.0, 1000.0, True)
+    op = Operator(N, nz, kh, kv, delta, 2, precision=precision, max_batch=8)
+    b = torch.from_numpy(workloads.rhs(N, nz)[0]).cuda()
+    ref = op.solve(b, rtol=1e-8)
+    op.profile(True)
+    got = op.solve(b, rtol=1e-8)
+    _, n, by = op.profile_read(_lib.PROF_SWEEP_FINE)
+    op.profile(False)
+    assert got.iters == ref.iters and torch.equal(got.x, ref.x)
+    assert n == 2 * got.iters[0] and by == n * 7 * word * nz * 6 * N * N
