@@ -165,7 +165,8 @@ int helmholtz_update(helmholtz_t h, const double* kh, const double* kv, const do
 int helmholtz_destroy(helmholtz_t h);
 
 /* y = H x on the finest level (the operator of Eq. helmholtz), float64,
- * x and y [batch][nz][ncol], must not overlap. Asynchronous. */
+ * x and y [batch][nz][ncol]; they may overlap (then x is copied first).
+ * Asynchronous. */
 int helmholtz_apply(helmholtz_t h, const double* x, double* y, int32_t batch,
                     helmholtz_stream_t stream);
 
@@ -174,7 +175,7 @@ int helmholtz_apply(helmholtz_t h, const double* x, double* y, int32_t batch,
  * This is also the preconditioner-only solver PreOnly(H, M) of Section 4.1:
  * with nlevels = 1 it is the line relaxation P_H^(Jac)(omega, n_coarse),
  * n_coarse block-Jacobi sweeps (Eq. jacobi) from x = 0.
- * b and x [batch][nz][ncol] float64, must not overlap. Asynchronous. */
+ * b and x [batch][nz][ncol] float64; they may overlap. Asynchronous. */
 int helmholtz_vcycle(helmholtz_t h, const double* b, double* x, int32_t batch,
                      helmholtz_stream_t stream);
 
@@ -195,13 +196,13 @@ int helmholtz_vcycle(helmholtz_t h, const double* b, double* x, int32_t batch,
  * on (else HELMHOLTZ_EINVAL). Returns HELMHOLTZ_ESCRATCH, launching nothing,
  * when the level vectors exceed the array: e.g. C96 x 30 with 5 levels fits
  * at batch 1 in float64 and at batch 2 in float32, C192 x 70 does not.
- * b and x [batch][nz][ncol] float64, must not overlap. Asynchronous. */
+ * b and x [batch][nz][ncol] float64; they may overlap. Asynchronous. */
 #define HELMHOLTZ_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 int helmholtz_vcycle_noalloc(helmholtz_t h, const double* b, double* x, int32_t batch,
                              helmholtz_stream_t stream);
 
 /* Same V-cycle entirely in float32 (coefficients, vectors and accumulation).
- * b and x [batch][nz][ncol] float32, must not overlap. Asynchronous. */
+ * b and x [batch][nz][ncol] float32; they may overlap. Asynchronous. */
 int helmholtz_vcycle_f32(helmholtz_t h, const float* b, float* x, int32_t batch,
                          helmholtz_stream_t stream);
 

@@ -1225,12 +1225,22 @@ size_t carve_levels(const helmholtz_s* h, uintptr_t base, int batch, VBufs<T>& V
     return cv.off;
 }
 
+// Whether the caller's vectors a and b ([batch][nz][ncol]) share memory.
+template <typename S>
+bool overlap(const helmholtz_s* h, const S* a, const S* b, int batch) {
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return (p < q ? q - p : p - q) < uintptr_t(batch) * uintptr_t(h->n) * sizeof(S);
+}
+
 // One V-cycle from the ABI layout to the ABI layout, in V; bt and xt are the
-// tiled vectors of the finest level.
+// tiled vectors of the finest level. On patches the last leg reads b of the
+// columns around a patch while other workgroups store x, so where the two
+// overlap the conversion passes run: all of b is then read before any of x is
+// written, as it is by the first and the last of the single sweeps.
 template <typename T, typename S>
 int vcycle_abi(helmholtz_s* h, const VBufs<T>& V, T* bt, T* xt, const S* b, S* x, int batch,
                hipStream_t s) {
-    if (abi_within<T>(h)) {
+    if (abi_within<T>(h) && !(on_patches<T>(h, 0) && overlap(h, b, x, batch))) {
         const AbiVectors io{b, x, sizeof(S) != sizeof(T)};
         vcycle_level<T>(h, V, 0, bt, xt, batch, nullptr, s, &io);
     } else {
@@ -1538,7 +1548,14 @@ int helmholtz_apply(helmholtz_t h, const double* x, double* y, int32_t batch,
     if (int e = check_batch(h, batch)) return e;
     if (!x || !y) return HELMHOLTZ_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    launch_apply_natural(h, x, y, batch, s);
+    if (overlap(h, x, y, batch)) {
+        // y would overwrite x that other workgroups have yet to read
+        retile<double, double, true>(h, x, h->p, batch, s);
+        launch_apply<double>(h, 0, h->p, h->q, batch, kDotXY, nullptr, s);
+        retile<double, double, false>(h, h->q, y, batch, s);
+    } else {
+        launch_apply_natural(h, x, y, batch, s);
+    }
     return last_error();
 }
 
