@@ -410,7 +410,9 @@ k_finalize(CgState st, int mode, int cnt, int seq, double rtol2) {
     double a1 = thread_partials<kFinBlock, 8>((upd ? st.partial3 : st.partial) + at, cnt);
     double a2 = 0.0;
     if (two) a2 = thread_partials<kFinBlock, 8>((upd ? st.partial4 : st.partial2) + at, cnt);
-    const bool live = mode == kFinBB || active != 0;
+    // a breakdown that the use of alpha found (bicg_alpha) ends the iteration here
+    const bool broke = mode == kFinBiRR && c[kBreak] != 0.0;
+    const bool live = mode == kFinBB || (active != 0 && !broke);
     if (!live && !publish) return;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -490,8 +492,9 @@ k_finalize(CgState st, int mode, int cnt, int seq, double rtol2) {
         default:
             break;
     }
+    if (broke) active = 0;
+    if (live || broke) st.active[rhs] = active;
     if (live) {
-        st.active[rhs] = active;
 #pragma unroll
         for (int i = 0; i < kScal; ++i) v[i] = c[i];
     }
@@ -554,8 +557,10 @@ __device__ __forceinline__ double cg_beta(const CgState& st, int rhs, int cnt, i
     return beta;
 }
 
-// BiCGStab: alpha = rho / (r0, v); zero (r0, v) ends the right-hand side (then
-// ok is false). omega = (t, s) / (t, t).
+// BiCGStab: alpha = rho / (r0, v); zero (r0, v) ends the right-hand side: ok is
+// false, and the breakdown is recorded for the kernels that follow. (active stays
+// as it is, which this kernel's other workgroups test: k_finalize clears it.)
+// omega = (t, s) / (t, t).
 __device__ __forceinline__ double bicg_alpha(const CgState& st, int rhs, int cnt, bool keep,
                                              bool* ok, double* sh) {
     double* v = st.sc + rhs * kScal;
@@ -566,12 +571,8 @@ __device__ __forceinline__ double bicg_alpha(const CgState& st, int rhs, int cnt
     *ok = rv != 0.0;
     const double alpha = *ok ? rho / rv : 0.0;
     if (keep && threadIdx.x == 0) {
-        if (*ok) {
-            v[kAlpha] = alpha;
-        } else {
-            v[kBreak] = 1.0;
-            st.active[rhs] = 0;
-        }
+        if (*ok) v[kAlpha] = alpha;
+        else v[kBreak] = 1.0;
     }
     return alpha;
 }
@@ -1796,7 +1797,7 @@ k_bicg_xr(double* __restrict__ x, double* __restrict__ r, const Z* __restrict__ 
           CgState st, int cnt) {
     __shared__ double sh[kBlock / 64];
     const TileGrid g = tile_grid(ncol);
-    if (!st.active[g.rhs]) return;
+    if (!st.active[g.rhs] || st.sc[g.rhs * kScal + kBreak] != 0.0) return;
     const double alpha = st.sc[g.rhs * kScal + kAlpha];
     const double omega = bicg_omega(st, g.rhs, cnt, g.tile == 0, sh);
     const int64_t n = int64_t(nz) * ncol;
