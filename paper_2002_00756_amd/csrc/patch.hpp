@@ -254,6 +254,12 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
     // the level at the thread's place j (-1: a pad), and one to load from
     auto level = [&](int j) { return at.level(pl + patch_place(j)); };
     auto from = [&](int j) { return uint32_t(max(level(j), 0)); };
+    // pads hold zero where a column solve starts and where it scales by the
+    // pivots, whatever their neighbours hold (zero times an infinity is not)
+    uint32_t pads = 0;
+#pragma unroll
+    for (int j = 0; j < JMAX; ++j) pads |= level(j) < 0 ? 1u << j : 0u;
+    auto row = [&](int j, T v) { return pads >> j & 1u ? T(0) : v; };
     const uint32_t o = uint32_t(c * nz);
     if (pl == 0 && lq < NCP) cols[lq] = c;
     T* Rq = R + lq * S + pl;
@@ -329,7 +335,7 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
 #pragma unroll
         for (int j = 0; j < JMAX; ++j) {
             Cq[patch_place(j)] = vc[j];
-            vb[j] = level(j) < 0 ? T(0) : vb[j];
+            vb[j] = row(j, vb[j]);
             if constexpr (SC == kRowW) vb[j] = vb[j] / so[j];
         }
     }
@@ -418,7 +424,7 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
                 }
             }
 #pragma unroll
-            for (int j = 0; j < JMAX; ++j) Rq[patch_place(j)] = r[j];
+            for (int j = 0; j < JMAX; ++j) Rq[patch_place(j)] = zero ? r[j] : row(j, r[j]);
         }
         // what the next phases read from memory arrives during the solve
         if constexpr (HOLD && LEG != kUp) {
@@ -443,7 +449,7 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
 #pragma unroll
             for (int j = 0; j < JMAX; ++j) {
                 v[j] = Rq[patch_place(j)];
-                v[j] = mo[j] * (pl + patch_place(j) == HMAX ? v[j] + e : v[j]);
+                v[j] = row(j, mo[j] * (pl + patch_place(j) == HMAX ? v[j] + e : v[j]));
             }
 #pragma unroll
             for (int j = 0; j < JMAX; ++j) Rq[patch_place(j)] = v[j];
