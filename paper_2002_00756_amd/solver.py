@@ -166,6 +166,16 @@ class Operator:
             raise ValueError(f"batch {v.shape[0]} exceeds max_batch {self.max_batch}")
         return v, squeeze
 
+    def _out(self, out, b):
+        """The array that receives a result of ``b``'s shape: ``out``, which the library
+        writes as ``[batch][nz][ncol]`` float64 on this device, or a new one."""
+        if out is None:
+            return torch.empty_like(b)
+        x = out.view(b.shape)
+        if x.dtype != torch.float64 or x.device != self.device or not x.is_contiguous():
+            raise ValueError(f"out must be contiguous float64 on {self.device}")
+        return x
+
     # -- operations --------------------------------------------------------
     def apply(self, x, _fn="helmholtz_apply"):
         """y = H x (float64)."""
@@ -191,9 +201,9 @@ class Operator:
         """``vcycle`` with the level vectors in the library's static scratch array
         instead of the workspace (for callers that cannot allocate; calls on one
         GPU must not overlap). ``out`` receives x when given (then nothing is
-        allocated here either)."""
+        allocated here either); it may be ``b`` itself."""
         b, sq = self._vec(b)
-        x = torch.empty_like(b) if out is None else out.view(b.shape)
+        x = self._out(out, b)
         _lib.check(self.lib.helmholtz_vcycle_noalloc(self._h, b.data_ptr(), x.data_ptr(),
                                                      b.shape[0], _stream_ptr(self.device)),
                    "helmholtz_vcycle_noalloc")
@@ -220,7 +230,7 @@ class Operator:
         """Preconditioned Krylov solve (the handle's ``cg`` method) from x = 0; returns
         the solution and per-RHS statistics."""
         b, sq = self._vec(b)
-        x = torch.empty_like(b) if out is None else out.view(b.shape)
+        x = self._out(out, b)
         nb = b.shape[0]
         iters = (ctypes.c_int32 * nb)()
         rel = (ctypes.c_double * nb)()
