@@ -66,7 +66,9 @@ struct Level {
     int32_t* parent = nullptr;  // [ncol] into level + 1 (not on the coarsest)
     int32_t* pofs = nullptr;    // [3][ncol] prolongation offsets (not on the coarsest)
     int32_t* child = nullptr;   // [4][ncol] into level - 1 (not on the finest)
-    // small levels: patch size (index of kPatchShapes, -1: none) and its tables
+    // levels whose legs run on patches in float64 or float32 V-cycles: patch size
+    // (index of kPatchShapes, -1: neither) and its tables
+    bool patch64 = false, patch32 = false;
     int patch = -1, npatch = 0;
     int32_t* pcol = nullptr;
     int32_t* ppar = nullptr;
@@ -266,15 +268,18 @@ bool patch_pays(int kind, int nz, int places, int64_t columns, bool nine) {
     }
 }
 
-// Whether the legs of level l run on patches in one launch each (k_patch) in
-// V-cycles of precision T. A float32 handle never runs a float64 V-cycle.
+// Whether V-cycles of precision T run the legs of a level of ncol columns on
+// patches of this size, in one launch each (k_patch).
+template <typename T>
+bool patch_runs(const helmholtz_s* h, int kind, int ncol) {
+    const int jmax = patch_levels(h->nz, !h->nine && !h->weighted);
+    return patch_pays<T>(kind, h->nz, kPatchLanes * jmax, int64_t(ncol) * h->B, h->nine) &&
+           patch_lds_bytes<T>(kPatchShapes[kind].ncp, jmax) <= kLdsBytes;
+}
+
 template <typename T>
 bool patch_level(const helmholtz_s* h, int l) {
-    const Level& v = h->lev[l];
-    if (v.patch < 0 || (sizeof(T) == 8 && h->cfg.mg_precision == HELMHOLTZ_FP32)) return false;
-    const int jmax = patch_levels(h->nz, !h->nine && !h->weighted);
-    return patch_pays<T>(v.patch, h->nz, kPatchLanes * jmax, int64_t(v.ncol) * h->B, h->nine) &&
-           patch_lds_bytes<T>(kPatchShapes[v.patch].ncp, jmax) <= kLdsBytes;
+    return sizeof(T) == 8 ? h->lev[l].patch64 : h->lev[l].patch32;
 }
 
 void layout(helmholtz_s* h, Carver& cv) {
@@ -377,7 +382,13 @@ void init_shape(helmholtz_s* h, const helmholtz_config* cfg) {
         v.ncol = 6 * v.N * v.N;
         v.ncolp = (v.ncol + kTile - 1) / kTile * kTile;
         v.nvp = cfg->nz * v.ncolp;
-        v.patch = patch_kind(cfg, v.N, l == h->L - 1);
+        const int kind = patch_kind(cfg, v.N, l == h->L - 1);
+        if (kind >= 0) {
+            // a float32 handle never runs a float64 V-cycle
+            v.patch64 = cfg->mg_precision == HELMHOLTZ_FP64 && patch_runs<double>(h, kind, v.ncol);
+            v.patch32 = patch_runs<float>(h, kind, v.ncol);
+        }
+        if (v.patch64 || v.patch32) v.patch = kind;
         if (v.patch >= 0)
             v.npatch = patch_count(v.N, kPatchShapes[v.patch].pw, kPatchShapes[v.patch].ph);
     }
