@@ -241,39 +241,57 @@ int patch_kind(const helmholtz_config* c, int N, bool coarsest) {
     return cols <= 1000 ? 0 : (cols <= 4096 ? 1 : (cols <= 40000 ? 4 : -1));
 }
 
-// Whether a patch of this size pays on columns of nz levels: the deeper ones
-// need more registers than a workgroup of that size has (the values spill:
-// coarsest level C24 x 70 52 / 36 us), or the level's traffic, multiplied by
-// the rings, outgrows what the launches cost. On patches the columns have
-// `places` rows, pads included (32 at least, 64 with the 9-cell and the weighted
-// operators), so with 8 x 4 patches it is the padded vector that counts: up to
-// 2.5 MiB they gain (two levels, on patches / kernel by kernel: C40 x 2 9-cell
-// float32, 2.3 MiB, 35 / 41 us; C54 x 6 float32, 2.1 MiB, 32 / 46; but C54 x 6
-// 9-cell float32, 4.3 MiB, 53 / 48, C42 x 2 twice, weighted float64, 10 MiB, 86 /
-// 44), and to 3.5 where three fifths of the places are levels (C64 x 20 float32,
-// 3.0 MiB, 45 / 50; C48 x 47, 3.4 MiB, 81 / 85; C48 x 70, 5.1 MiB, 108 / 106).
+// Whether the legs pay on patches, on columns of nz levels in `places` rows (fill
+// rows included: 16 at least, 32 with the 9-cell and the weighted operators).
+// A CU holds one workgroup of a leg on deep columns, so a leg's time goes with the
+// generations of 256 workgroups that it takes, whole ones, while kernel by kernel
+// it goes with the values. V-cycles, this level on patches / kernel by kernel (us,
+// two levels, coarsest level on patches both ways, float32 unless noted):
+// * 8 x 4 patches, one generation: gain at all depths that the registers hold
+//   (patch_deepest): C32 x 32 27 / 45, C32 x 80 61 / 87, C32 x 48 float64 56 / 68;
+// * two: up to 64 rows (C40 x 64 64 / 69, C40 x 70 91 / 83; 9-cell C40 x 47 70 /
+//   79), in float64 up to 32 (C40 x 30 48 / 51, C40 x 47 87 / 69), and not for the
+//   few levels whose columns are mostly fill (9-cell C40 x 2 37.2 / 35.6; float64
+//   C40 x 1 48 / 36, C40 x 20 54 / 59);
+// * three: float32, up to 32 rows (C54 x 6 30 / 35, C54 x 30 52 / 57, C54 x 40 74 /
+//   70; 9-cell C54 x 6 57 / 49; float64 C54 x 10 46 / 44); four: 16 rows (C72 x 10
+//   44 / 49, C72 x 30 74 / 72); five no more (C80 x 8 50 / 47);
+// * levels below kSmallSweepCols columns in a batch, which kernel by kernel run
+//   with the narrow tiles, take one generation more beyond the second (C24 x 30
+//   float64, six right-hand sides 73 / 82).
+// 4 x 4 patches need less of a CU, so only the deep columns lose to a second
+// generation (C24 x 100 58 / 70, C26 x 100 94 / 80; 9-cell C26 x 48 46 / 60, x 64
+// 71 / 66; coarsest level C20 x 48 float64 19 / 31, C26 x 48 35 / 33), with the
+// weighted operator not once it is half full (C32 x 48 float64 37 / 46).
 template <typename T>
-bool patch_pays(int kind, int nz, int places, int64_t columns, bool nine) {
+bool patch_pays(int kind, int nz, int places, int ncol, int64_t workgroups, bool nine,
+                bool weighted) {
     constexpr bool f32 = sizeof(T) == 4;
-    switch (kind) {
-        case 0:
-        case 2: return !nine || nz <= (f32 ? 80 : 48);
-        case 1: return nz <= (nine ? (f32 ? 80 : 48) : (f32 ? HELMHOLTZ_NZ_MAX : 80));
-        case 3: return nz <= (nine ? 32 : (f32 ? 64 : 48));
-        default: {
-            const int64_t kib = columns * places * int64_t(sizeof(T)) >> 10;
-            return kib <= (5 * nz >= 3 * places ? 3584 : 2560) &&
-                   nz <= (nine ? (f32 ? 48 : 32) : (f32 ? 80 : 64));
-        }
+    constexpr int kWave = 256;  // workgroups of one generation
+    if (nz > patch_deepest<T>(kind, nine)) return false;
+    const int64_t gen = (workgroups + kWave - 1) / kWave;
+    if (gen == 1 || kind == 0 || kind == 2) return true;
+    const int fill = places - nz;
+    if (kind == 1) return places <= (nine || weighted ? 48 : 80);
+    if (kind == 3)
+        return (gen == 2 || f32) &&
+               places * int(sizeof(T)) <= (weighted && 2 * workgroups >= 3 * kWave ? 384 : 256);
+    switch (gen > 2 && ncol < kSmallSweepCols && !nine ? gen - 1 : gen) {
+        case 2: return f32 ? places <= 64 && fill <= 28 : places <= 32 && fill <= 13;
+        case 3: return f32 && places <= 32 && fill <= (nine ? 4 : 12);
+        case 4: return f32 && places <= 16 && fill <= 12;
+        default: return false;
     }
 }
 
 // Whether V-cycles of precision T run the legs of a level of ncol columns on
 // patches of this size, in one launch each (k_patch).
 template <typename T>
-bool patch_runs(const helmholtz_s* h, int kind, int ncol) {
+bool patch_runs(const helmholtz_s* h, int kind, int ncol, int npatch) {
     const int jmax = patch_levels(h->nz, !h->nine && !h->weighted);
-    return patch_pays<T>(kind, h->nz, kPatchLanes * jmax, int64_t(ncol) * h->B, h->nine) &&
+    const int64_t workgroups = int64_t(h->B) * npatch;
+    return patch_pays<T>(kind, h->nz, kPatchLanes * jmax, ncol, workgroups, h->nine,
+                         h->weighted) &&
            patch_lds_bytes<T>(kPatchShapes[kind].ncp, jmax) <= kLdsBytes;
 }
 
@@ -383,14 +401,15 @@ void init_shape(helmholtz_s* h, const helmholtz_config* cfg) {
         v.ncolp = (v.ncol + kTile - 1) / kTile * kTile;
         v.nvp = cfg->nz * v.ncolp;
         const int kind = patch_kind(cfg, v.N, l == h->L - 1);
-        if (kind >= 0) {
-            // a float32 handle never runs a float64 V-cycle
-            v.patch64 = cfg->mg_precision == HELMHOLTZ_FP64 && patch_runs<double>(h, kind, v.ncol);
-            v.patch32 = patch_runs<float>(h, kind, v.ncol);
-        }
-        if (v.patch64 || v.patch32) v.patch = kind;
-        if (v.patch >= 0)
-            v.npatch = patch_count(v.N, kPatchShapes[v.patch].pw, kPatchShapes[v.patch].ph);
+        if (kind < 0) continue;
+        const int np = patch_count(v.N, kPatchShapes[kind].pw, kPatchShapes[kind].ph);
+        // a float32 handle never runs a float64 V-cycle
+        v.patch64 = cfg->mg_precision == HELMHOLTZ_FP64 &&
+                    patch_runs<double>(h, kind, v.ncol, np);
+        v.patch32 = patch_runs<float>(h, kind, v.ncol, np);
+        if (!v.patch64 && !v.patch32) continue;
+        v.patch = kind;
+        v.npatch = np;
     }
     h->n = int64_t(cfg->nz) * h->lev[0].ncol;
     h->nvp = h->lev[0].nvp;

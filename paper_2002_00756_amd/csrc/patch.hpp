@@ -87,6 +87,22 @@ inline int patch_levels(int nz, bool seven_point) {
     return 0;
 }
 
+// Deepest column that a patch size is taken for: beyond it a thread's values
+// spill, and the legs lose to single kernels even where every workgroup has a CU
+// (V-cycles take, times as long on patches: coarsest level C14 x 100 float32 1.34,
+// C14 x 64 9-cell float64 3.1; C28 x 60 9-cell float32 1.19, float64 1.03).
+template <typename T>
+constexpr int patch_deepest(int kind, bool nine) {
+    constexpr bool f32 = sizeof(T) == 4;
+    switch (kind) {
+        case 0:
+        case 2: return nine ? (f32 ? 80 : 48) : kNzMax;
+        case 1: return nine ? (f32 ? 80 : 48) : (f32 ? kNzMax : 80);
+        case 3: return nine ? 32 : (f32 ? 64 : 48);
+        default: return nine ? (f32 ? 48 : 32) : (f32 ? 80 : 48);
+    }
+}
+
 // LDS stride of a column: an odd number of values, so that lanes on
 // neighbouring columns read different banks.
 constexpr int patch_stride(int jmax) { return kPatchLanes * jmax + 1; }

@@ -1,0 +1,56 @@
+"""Which levels run on patches (host side): sizes at which both routes were timed,
+one generation of workgroups after the other, shallow and deep columns. The route
+shows in the workspace, which holds coefficients of its own for each precision that
+runs a level on patches; three presmoothing sweeps keep the finest level off them
+and leave the coarsest as it is."""
+import ctypes
+
+import pytest
+
+from paper_2002_00756_amd import _lib
+
+PLANES = 9
+
+
+def _bytes(N, nz, n_pre, precision, form, batch):
+    cfg = _lib.Config(N, nz, 2, n_pre, 2, 4, 0.8, precision,
+                      _lib.BICGSTAB if form == "weighted" else _lib.CG_STANDARD, batch,
+                      9 if form == "nine" else 7, int(form == "weighted"))
+    n = _lib.load().helmholtz_workspace_bytes(ctypes.byref(cfg))
+    assert n
+    return n
+
+
+def _places(nz, form):
+    sizes = (16, 32, 48, 64, 80, 128) if form == "sym" else (32, 48, 80, 128)
+    return next(p for p in sizes if nz <= p)
+
+
+def _on_patches(N, nz, form, precision, batch):
+    own = _bytes(N, nz, 2, precision, form, batch) - _bytes(N, nz, 3, precision, form, batch)
+    # a float64 handle may hold float32 coefficients alone, half the size
+    return own >= PLANES * _places(nz, form) * 6 * N * N * (8 if precision == _lib.FP64 else 4)
+
+
+F64, F32 = _lib.FP64, _lib.FP32
+ROUTES = [  # N, nz, form, precision, batch, on patches
+    (32, 32, "sym", F32, 1, True), (32, 80, "sym", F32, 1, True), (32, 48, "sym", F64, 1, True),
+    (32, 60, "sym", F64, 1, False), (32, 1, "nine", F64, 1, True), (32, 60, "nine", F32, 1, False),
+    (40, 64, "sym", F32, 1, True), (40, 70, "sym", F32, 1, False), (40, 30, "sym", F64, 1, True),
+    (36, 40, "sym", F64, 1, False), (40, 47, "nine", F32, 1, True), (40, 2, "nine", F32, 1, False),
+    (40, 1, "sym", F64, 1, False), (40, 1, "weighted", F64, 1, False),
+    (40, 20, "nine", F64, 1, True), (44, 64, "weighted", F32, 1, False),
+    (54, 6, "sym", F32, 1, True), (54, 6, "nine", F32, 1, False), (54, 1, "sym", F32, 1, False),
+    (54, 30, "sym", F32, 1, True), (54, 40, "nine", F32, 1, False), (54, 6, "sym", F64, 1, False),
+    (54, 6, "weighted", F32, 1, False), (64, 20, "sym", F32, 1, True),
+    (72, 10, "sym", F32, 1, True), (72, 30, "sym", F32, 1, False), (80, 8, "sym", F32, 1, False),
+    (24, 100, "sym", F32, 1, True), (26, 100, "sym", F32, 1, False),
+    (26, 64, "nine", F32, 1, False), (26, 48, "nine", F32, 1, True),
+    (24, 30, "sym", F64, 6, True), (32, 30, "sym", F64, 3, False),
+    (12, 70, "sym", F32, 8, False), (12, 10, "sym", F64, 8, True),
+]
+
+
+@pytest.mark.parametrize("N,nz,form,precision,batch,on", ROUTES)
+def test_route(N, nz, form, precision, batch, on):
+    assert _on_patches(N, nz, form, precision, batch) == on
