@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <type_traits>
@@ -1414,10 +1415,12 @@ int create_impl(const helmholtz_config* cfg, const double* kh, const double* kv,
 
     // mesh tables of every level, built on the host and copied at once
     const int nz = h->nz;
-    std::vector<unsigned char> tables(h->table_bytes);
+    // (not cleared: every table is written whole)
+    std::unique_ptr<unsigned char[]> tables(new (std::nothrow) unsigned char[h->table_bytes]);
+    if (!tables) return fail(HELMHOLTZ_EINVAL);
     auto host = [&](auto* device) {  // where a table's host image stands
         return reinterpret_cast<decltype(device)>(
-            tables.data() + (reinterpret_cast<uintptr_t>(device) -
+            tables.get() + (reinterpret_cast<uintptr_t>(device) -
                              reinterpret_cast<uintptr_t>(workspace)));
     };
     std::vector<int32_t> ft;
@@ -1444,15 +1447,18 @@ int create_impl(const helmholtz_config* cfg, const double* kh, const double* kv,
             // prolongation offsets: the parent and the parents of the outward
             // E/W (W for even i, E for odd i) and N/S (S for even j, N for
             // odd j) neighbours, as tiled offsets on the coarse level
-            auto tb = [&](int32_t cc) { return (cc / kTile) * kTile * nz + cc % kTile; };
+            auto tb = [&](int32_t cc) { return (cc >> 5) * (kTile * nz) + (cc & (kTile - 1)); };
             int32_t* const po = host(v.pofs);
-            for (size_t c = 0; c < nc; ++c) {
-                const int i = int(c % v.N), j = int((c / v.N) % v.N);
+            for (size_t c = 0, i = 0, j = 0; c < nc; ++c) {
                 const int32_t ew = nbr[((i & 1) ? 0 : 1) * nc + c];
                 const int32_t ns = nbr[((j & 1) ? 2 : 3) * nc + c];
                 po[c] = tb(par[c]);
                 po[nc + c] = tb(par[ew]);
                 po[2 * nc + c] = tb(par[ns]);
+                if (++i == size_t(v.N)) {
+                    i = 0;
+                    if (++j == size_t(v.N)) j = 0;
+                }
             }
         }
         if (v.child) build_children(v.N, host(v.child));
@@ -1460,15 +1466,13 @@ int create_impl(const helmholtz_config* cfg, const double* kh, const double* kv,
             const PatchShape& S = kPatchShapes[v.patch];
             int32_t* const col = host(v.pcol);
             build_patches(v.N, nbr, S.pw, S.ph, S.depth, S.ncp, col, host(v.plnb), host(v.pcnt));
-            if (v.parent) {
-                const int32_t* par = host(v.parent);
-                int32_t* const ppar = host(v.ppar);
-                for (size_t i = 0; i < size_t(v.npatch) * S.ncp; ++i) ppar[i] = par[col[i]];
-            }
+            const int32_t* par = v.parent ? host(v.parent) : nullptr;
+            int32_t* const ppar = host(v.ppar);
+            for (size_t i = 0; i < size_t(v.npatch) * S.ncp; ++i) ppar[i] = par ? par[col[i]] : 0;
         }
     }
     // the host image must stay alive until the copy has run
-    if (hipMemcpyAsync(workspace, tables.data(), tables.size(), hipMemcpyHostToDevice, s) !=
+    if (hipMemcpyAsync(workspace, tables.get(), h->table_bytes, hipMemcpyHostToDevice, s) !=
             hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return fail(HELMHOLTZ_EHIP);

@@ -62,6 +62,13 @@ void build_neighbours(int N, int32_t* nbr) {
         for (int j = 0; j < N; ++j) {
             for (int i = 0; i < N; ++i) {
                 const int64_t c = int64_t(p) * N * N + int64_t(j) * N + i;
+                if (i > 0 && i + 1 < N && j > 0 && j + 1 < N) {
+                    nbr[c] = int32_t(c + 1);
+                    nbr[ncol + c] = int32_t(c - 1);
+                    nbr[2 * ncol + c] = int32_t(c + N);
+                    nbr[3 * ncol + c] = int32_t(c - N);
+                    continue;
+                }
                 const Vec3 centre = O + (2 * i + 1) * P.east + (2 * j + 1) * P.north;
                 for (int d = 0; d < 4; ++d) {
                     const int i2 = i + di[d], j2 = j + dj[d];
@@ -121,30 +128,50 @@ void build_children(int Nc, int32_t* child) {
 
 void build_patches(int N, const int32_t* nbr, int pw, int ph, int depth, int ncp, int32_t* cols,
                    uint32_t* lnbs, int32_t* cnts) {
-    const size_t ncol = 6 * size_t(N) * N, np = size_t(patch_count(N, pw, ph));
-    std::fill(lnbs, lnbs + np * ncp, 0u);
-    std::fill(cnts, cnts + np * 8, 0);
+    const size_t ncol = 6 * size_t(N) * N;
     std::vector<int32_t> place(ncol, -1);  // column -> place in the current list
-    size_t p = 0, like = np;
+    const size_t row = size_t((N + pw - 1) / pw);  // patches of one row of a panel
+    // whether a patch from x on keeps its rings within its panel along one axis,
+    // and so does the one before it
+    auto clear = [&](int x, int size) { return x >= size + depth && x + size + depth <= N; };
+    size_t p = 0;
     for (int pan = 0; pan < 6; ++pan)
         for (int j0 = 0; j0 < N; j0 += ph)
             for (int i0 = 0; i0 < N; i0 += pw, ++p) {
                 const int w = std::min(pw, N - i0), h = std::min(ph, N - j0);
+                const int32_t first = int32_t((int64_t(pan) * N + j0) * N + i0);
                 int32_t* col = cols + p * ncp;
                 int32_t* cnt = cnts + p * 8;
                 uint32_t* lnb = lnbs + p * ncp;
-                // a patch whose rings stay inside its panel is a shifted copy of
-                // the first such one
-                const bool inner = i0 >= depth && i0 + pw + depth <= N && j0 >= depth &&
-                                   j0 + ph + depth <= N;
-                if (inner && like < np) {
-                    const int32_t by = int32_t((int64_t(pan) * N + j0) * N + i0) - cols[like * ncp];
-                    for (int q = 0; q < ncp; ++q) col[q] = cols[like * ncp + q] + by;
+                // Along an axis on which its rings stay inside the panel, a patch is
+                // the one before it, shifted: its panel's columns by one patch, those
+                // across the panel edge (one edge at most) by that on the other panel.
+                const bool right = clear(i0, pw) && h == ph, up = clear(j0, ph) && w == pw;
+                if (right || up) {
+                    const size_t like = right ? p - 1 : p - row;
+                    const int32_t by = right ? pw : ph * N;
+                    // the edge that the other axis reaches, if any: a column on it
+                    int d, at;
+                    if (right) {
+                        d = j0 < depth ? 3 : 2;
+                        at = (pan * N + (d == 3 ? 0 : N - 1)) * N + i0;
+                    } else {
+                        d = i0 < depth ? 1 : 0;
+                        at = (pan * N + j0) * N + (d == 1 ? 0 : N - 1);
+                    }
+                    const int32_t* nd = nbr + d * ncol;
+                    const int32_t across = nd[at] - nd[at - by];
+                    const int32_t base = pan * N * N;
+                    const int32_t* from = cols + like * ncp;
+                    for (int q = 0; q < ncp; ++q)
+                        col[q] = from[q] +
+                                 (uint32_t(from[q] - base) < uint32_t(N * N) ? by : across);
                     std::copy_n(cnts + like * 8, 8, cnt);
                     std::copy_n(lnbs + like * ncp, ncp, lnb);
                     continue;
                 }
-                if (inner) like = p;
+                std::fill_n(cnt, 8, 0);
+                std::fill_n(lnb, ncp, 0u);
                 int n = 0;
                 auto add = [&](int32_t c) {
                     if (place[c] < 0) {
@@ -152,9 +179,8 @@ void build_patches(int N, const int32_t* nbr, int pw, int ph, int depth, int ncp
                         col[n++] = c;
                     }
                 };
-                for (int j = j0; j < j0 + h; ++j)
-                    for (int i = i0; i < i0 + w; ++i)
-                        add(int32_t((int64_t(pan) * N + j) * N + i));
+                for (int j = 0; j < h; ++j)
+                    for (int i = 0; i < w; ++i) add(first + j * N + i);
                 cnt[4] = w;
                 cnt[0] = n;
                 for (int r = 1; r <= depth; ++r) {
