@@ -27,7 +27,6 @@ namespace {
 constexpr int kRedBlocks = 2048;  // partial sums per right-hand side for vector reductions
 constexpr int kMaxLevels = kSetupLevels;
 constexpr int kApplyChunk = 4;   // vertical levels per thread in apply / residual kernels
-constexpr size_t kLdsBytes = size_t(160) << 10;  // LDS of one workgroup
 constexpr int kSmallSweepCols = 5000;  // levels below this use narrow sweep tiles
 
 // Per-level arrays use the column-tile layout of the kernels (element (k, c)
@@ -289,11 +288,11 @@ bool patch_pays(int kind, int nz, int places, int ncol, int64_t workgroups, bool
 // patches of this size, in one launch each (k_patch).
 template <typename T>
 bool patch_runs(const helmholtz_s* h, int kind, int ncol, int npatch) {
-    const int jmax = patch_levels(h->nz, !h->nine && !h->weighted);
-    const int64_t workgroups = int64_t(h->B) * npatch;
-    return patch_pays<T>(kind, h->nz, kPatchLanes * jmax, ncol, workgroups, h->nine,
-                         h->weighted) &&
-           patch_lds_bytes<T>(kPatchShapes[kind].ncp, jmax) <= kLdsBytes;
+    const bool seven_point = !h->nine && !h->weighted;
+    const int jmax = patch_levels(h->nz, seven_point);
+    return patch_compiled<T>(kind, jmax, h->nine, seven_point) &&
+           patch_pays<T>(kind, h->nz, kPatchLanes * jmax, ncol, int64_t(h->B) * npatch, h->nine,
+                         h->weighted);
 }
 
 template <typename T>

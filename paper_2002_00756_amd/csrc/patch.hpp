@@ -79,7 +79,7 @@ constexpr int kPatchKinds = int(sizeof(kPatchShapes) / sizeof(kPatchShapes[0]));
 // Levels per thread that are compiled for: every thread works on JMAX places
 // without range tests (a test per place splits the loop into blocks that each
 // wait for LDS).
-inline int patch_levels(int nz, bool seven_point) {
+constexpr int patch_levels(int nz, bool seven_point) {
     const int jn = (nz + kPatchLanes - 1) / kPatchLanes;
     const int sizes[] = {2, 4, 6, 8, 10, 16};
     for (int j : sizes)
@@ -125,12 +125,22 @@ struct ColumnPlaces {
     }
 };
 
+constexpr size_t kLdsBytes = size_t(160) << 10;  // LDS that one workgroup may take
+
 // LDS of one workgroup: right-hand side, factor and iterate per place, two
 // values and a table entry per column.
 template <typename T>
-inline size_t patch_lds_bytes(int ncp, int jmax) {
+constexpr size_t patch_lds_bytes(int ncp, int jmax) {
     return (3 * size_t(patch_stride(jmax)) * ncp + 2 * ncp) * sizeof(T) +
            size_t(ncp) * sizeof(int32_t);
+}
+
+// Whether a patch size is compiled for jmax levels per thread: some column that
+// it is taken for needs that many, and its workgroup fits the LDS.
+template <typename T>
+constexpr bool patch_compiled(int kind, int jmax, bool nine, bool seven_point) {
+    return patch_levels(patch_deepest<T>(kind, nine), seven_point) >= jmax &&
+           patch_lds_bytes<T>(kPatchShapes[kind].ncp, jmax) <= kLdsBytes;
 }
 
 // Whether the couplings stay in registers from one sweep of a leg to the next
@@ -605,8 +615,10 @@ void launch_patch(int kind, int leg, bool nine, bool weighted, const PatchArgs<T
 template <typename T, int KIND, int JMAX, int LEG, bool K2, int SC>
 void launch_patch_one(const PatchArgs<T>& A, hipStream_t s) {
     constexpr PatchShape S = kPatchShapes[KIND];
-    hipLaunchKernelGGL((k_patch<T, KIND, JMAX, LEG, K2, SC>), dim3(A.P.npatch * A.batch),
-                       dim3(S.threads()), patch_lds_bytes<T>(S.ncp, JMAX), s, A);
+    // (no other size is selected: patch_runs)
+    if constexpr (patch_compiled<T>(KIND, JMAX, K2, !K2 && SC == kSym))
+        hipLaunchKernelGGL((k_patch<T, KIND, JMAX, LEG, K2, SC>), dim3(A.P.npatch * A.batch),
+                           dim3(S.threads()), patch_lds_bytes<T>(S.ncp, JMAX), s, A);
 }
 
 template <typename T, int KIND, int LEG, bool K2, int SC>
