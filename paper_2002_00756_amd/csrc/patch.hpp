@@ -103,6 +103,14 @@ constexpr int patch_deepest(int kind, bool nine) {
     }
 }
 
+// The next smaller size compiled, 0 for the smallest.
+constexpr int patch_below(int jmax, bool seven_point) {
+    int below = 0;
+    for (int nz = kPatchLanes; nz < kPatchLanes * jmax; nz += kPatchLanes)
+        if (patch_levels(nz, seven_point) < jmax) below = patch_levels(nz, seven_point);
+    return below;
+}
+
 // LDS stride of a column: an odd number of values, so that lanes on
 // neighbouring columns read different banks.
 constexpr int patch_stride(int jmax) { return kPatchLanes * jmax + 1; }
@@ -281,11 +289,23 @@ __global__ void __launch_bounds__(kPatchShapes[KIND].threads()) k_patch(PatchArg
     auto level = [&](int j) { return at.level(pl + patch_place(j)); };
     auto from = [&](int j) { return uint32_t(max(level(j), 0)); };
     // pads hold zero where a column solve starts and where it scales by the
-    // pivots, whatever their neighbours hold (zero times an infinity is not)
-    uint32_t pads = 0;
-#pragma unroll
-    for (int j = 0; j < JMAX; ++j) pads |= level(j) < 0 ? 1u << j : 0u;
-    auto row = [&](int j, T v) { return pads >> j & 1u ? T(0) : v; };
+    // pivots, whatever their neighbours hold (zero times an infinity is not).
+    // Each half has more rows than half the next smaller size has places, which
+    // leaves most places without a test; a mask of the thread's pads, held, took
+    // 704-thread workgroups over the registers of two on a CU (down leg C48 x 30
+    // float32 12.4 -> 16.2 us).
+    constexpr int ROWS = KL * patch_below(JMAX, !K2 && SC == kSym) / 2;
+    const int end = HMAX + nz - A.mid;  // first place below the last row
+    auto row = [&](int j, T v) {
+        const int q = patch_place(j);
+        const bool top = q < HMAX && q + 2 * KL - 2 >= ROWS;  // may hold pads of that half
+        const bool bottom = q + 2 * KL - 2 > HMAX + ROWS;
+        bool pad = false;
+        if (top) pad = q + 2 * KL - 2 < HMAX ? pl >= A.mid - q
+                                              : uint32_t(pl - (A.mid - q)) < uint32_t(HMAX - A.mid);
+        if (bottom) pad = pad || pl >= end - q;
+        return pad ? T(0) : v;
+    };
     const uint32_t o = uint32_t(c * nz);
     if (pl == 0 && lq < NCP) cols[lq] = c;
     T* Rq = R + lq * S + pl;
