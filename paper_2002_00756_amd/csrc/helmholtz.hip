@@ -243,26 +243,28 @@ int patch_kind(const helmholtz_config* c, int N, bool coarsest) {
 
 // Whether the legs pay on patches, on columns of nz levels in `places` rows (fill
 // rows included: 16 at least, 32 with the 9-cell and the weighted operators).
-// A CU holds one workgroup of a leg on deep columns, so a leg's time goes with the
-// generations of 256 workgroups that it takes, whole ones, while kernel by kernel
-// it goes with the values. V-cycles, this level on patches / kernel by kernel (us,
-// two levels, coarsest level on patches both ways, float32 unless noted):
+// A CU holds one workgroup of a leg on deep columns (two on those of up to 32
+// float32 rows), so a leg's time goes with the generations of 256 workgroups that
+// it takes, whole ones, while kernel by kernel it goes with the values. V-cycles,
+// this level on patches / kernel by kernel (us, two levels, the coarsest on patches
+// both ways, float32 unless noted):
 // * 8 x 4 patches, one generation: gain at all depths that the registers hold
-//   (patch_deepest): C32 x 32 27 / 45, C32 x 80 61 / 87, C32 x 48 float64 56 / 68;
-// * two: up to 64 rows (C40 x 64 64 / 69, C40 x 70 91 / 83; 9-cell C40 x 47 70 /
-//   79), in float64 up to 32 (C40 x 30 48 / 51, C40 x 47 87 / 69), and not for the
-//   few levels whose columns are mostly fill (9-cell C40 x 2 37.2 / 35.6; float64
-//   C40 x 1 48 / 36, C40 x 20 54 / 59);
-// * three: float32, up to 32 rows (C54 x 6 30 / 35, C54 x 30 52 / 57, C54 x 40 74 /
-//   70; 9-cell C54 x 6 57 / 49; float64 C54 x 10 46 / 44); four: 16 rows (C72 x 10
-//   44 / 49, C72 x 30 74 / 72); five no more (C80 x 8 50 / 47);
+//   (patch_deepest): C32 x 32 26 / 44, C32 x 80 58 / 86, C32 x 48 float64 50 / 68;
+// * two: up to 64 rows (C40 x 64 63 / 68, C40 x 70 85 / 83; 9-cell C40 x 47 70 /
+//   79), in float64 up to 32 (C40 x 30 48 / 52, C40 x 47 76 / 69), and not for the
+//   few levels whose columns are mostly fill (9-cell C36 x 1 31 / 30; float64 C40
+//   x 1 30 / 25, 9-cell 48 / 34, x 20 53 / 58);
+// * three: float32, up to 32 rows (C54 x 6 30 / 36, C54 x 30 45 / 53, C54 x 40 74 /
+//   71; 9-cell C54 x 6 53 / 48; float64 C54 x 6 46 / 42); four: 16 rows (C72 x 10
+//   44 / 49, C72 x 40 105 / 92); five no more (C80 x 8 50 / 47);
 // * levels below kSmallSweepCols columns in a batch, which kernel by kernel run
 //   with the narrow tiles, take one generation more beyond the second (C24 x 30
-//   float64, six right-hand sides 73 / 82).
+//   float64, six right-hand sides 73 / 83).
 // 4 x 4 patches need less of a CU, so only the deep columns lose to a second
-// generation (C24 x 100 58 / 70, C26 x 100 94 / 80; 9-cell C26 x 48 46 / 60, x 64
-// 71 / 66; coarsest level C20 x 48 float64 19 / 31, C26 x 48 35 / 33), with the
-// weighted operator not once it is half full (C32 x 48 float64 37 / 46).
+// generation (C24 x 100 50 / 70, C26 x 100 81 / 80; 9-cell C26 x 48 46 / 59, x 64
+// 70 / 67; coarsest level C20 x 48 float64 19 / 31, C26 x 48 36 / 33), with the
+// weighted operator not once it is half full (C32 x 48 float64 36 / 46), and the
+// 9-cell ones of few levels in float64 (coarsest C25 x 4 23 / 22, C26 x 20 24 / 27).
 template <typename T>
 bool patch_pays(int kind, int nz, int places, int ncol, int64_t workgroups, bool nine,
                 bool weighted) {
@@ -272,6 +274,7 @@ bool patch_pays(int kind, int nz, int places, int ncol, int64_t workgroups, bool
     const int64_t gen = (workgroups + kWave - 1) / kWave;
     if (gen == 1 || kind == 0 || kind == 2) return true;
     const int fill = places - nz;
+    if (kind != 4 && nine && !f32 && fill > 13) return false;
     if (kind == 1) return places <= (nine || weighted ? 48 : 80);
     if (kind == 3)
         return (gen == 2 || f32) &&
