@@ -260,11 +260,13 @@ int patch_kind(const helmholtz_config* c, int N, bool coarsest) {
 // * levels below kSmallSweepCols columns in a batch, which kernel by kernel run
 //   with the narrow tiles, take one generation more beyond the second (C24 x 30
 //   float64, six right-hand sides 73 / 83).
-// 4 x 4 patches need less of a CU, so only the deep columns lose to a second
+// 4 x 4 patches need less of a CU: in float32 only the deep columns lose to a second
 // generation (C24 x 100 50 / 70, C26 x 100 81 / 80; 9-cell C26 x 48 46 / 59, x 64
-// 70 / 67; coarsest level C20 x 48 float64 19 / 31, C26 x 48 36 / 33), with the
-// weighted operator not once it is half full (C32 x 48 float64 36 / 46), and the
-// 9-cell ones of few levels in float64 (coarsest C25 x 4 23 / 22, C26 x 20 24 / 27).
+// 70 / 67). In float64 all deeper ones do (coarsest level C20 x 48 19 / 31, C26 x 48
+// 36 / 33), and, below a level that leaves nothing of theirs in the L2, those of
+// the larger stencils (times as long on patches: C26 in C104, 4 to 47 levels, 9-cell
+// 0.99 to 1.08, weighted with few levels 1.02; coarsest C25 to C32 in C50 to C64,
+// 9-cell 1.05, weighted with few levels 1.02, with 20 to 30 0.98).
 template <typename T>
 bool patch_pays(int kind, int nz, int places, int ncol, int64_t workgroups, bool nine,
                 bool weighted) {
@@ -274,11 +276,10 @@ bool patch_pays(int kind, int nz, int places, int ncol, int64_t workgroups, bool
     const int64_t gen = (workgroups + kWave - 1) / kWave;
     if (gen == 1 || kind == 0 || kind == 2) return true;
     const int fill = places - nz;
-    if (kind != 4 && nine && !f32 && fill > 13) return false;
-    if (kind == 1) return places <= (nine || weighted ? 48 : 80);
-    if (kind == 3)
-        return (gen == 2 || f32) &&
-               places * int(sizeof(T)) <= (weighted && 2 * workgroups >= 3 * kWave ? 384 : 256);
+    if (kind != 4) {
+        if (f32) return places <= (kind == 3 ? 64 : (nine || weighted ? 48 : 80));
+        return gen == 2 && !nine && fill <= 13 && places <= (kind == 1 && !weighted ? 48 : 32);
+    }
     switch (gen > 2 && ncol < kSmallSweepCols && !nine ? gen - 1 : gen) {
         case 2: return f32 ? places <= 64 && fill <= 28 : places <= 32 && fill <= 13;
         case 3: return f32 && places <= 32 && fill <= (nine ? 4 : 12);

@@ -46,7 +46,8 @@ ROUTES = [  # N, nz, form, precision, batch, on patches
     (72, 10, "sym", F32, 1, True), (72, 30, "sym", F32, 1, False), (80, 8, "sym", F32, 1, False),
     (24, 100, "sym", F32, 1, True), (26, 100, "sym", F32, 1, False),
     (26, 64, "nine", F32, 1, False), (26, 48, "nine", F32, 1, True),
-    (26, 1, "nine", F64, 1, False), (26, 20, "nine", F64, 1, True),
+    (26, 1, "nine", F64, 1, False), (26, 20, "nine", F64, 1, False),
+    (26, 40, "sym", F64, 1, True), (26, 70, "sym", F64, 1, False),
     (24, 30, "sym", F64, 6, True), (32, 30, "sym", F64, 3, False),
     (12, 70, "sym", F32, 8, False), (12, 10, "sym", F64, 8, True),
 ]
