@@ -7,9 +7,13 @@
 // levels as rows of 32 values:
 //     element (k, c) sits at tile_base(c) + 32 k,
 //     tile_base(c) = (c / 32) * 32 nz + c % 32.
-// For storage ncol is rounded up to ncolp, a multiple of 32; the padding
-// columns hold zeros (the workspace is cleared at set-up and no kernel writes
-// them), so reductions may run over the padded length. nvp = nz * ncolp.
+// For storage ncol is rounded up to ncolp, a multiple of 32. nvp = nz * ncolp.
+// The padding columns of the coefficients, of the Krylov vectors (r, p, q, z and
+// BiCGStab's) and of the finest level's right-hand side and solution hold zeros:
+// the workspace is cleared at set-up and no kernel writes them, so reductions over
+// these may run over the padded length. The Jacobi partner t of every level and
+// the right-hand side and solution of the coarser ones may hold anything there: the
+// legs on patches store them column by column in the same memory (patch.hpp).
 //   vectors        [batch][nvp]        tiled as above
 //   kh             [2][nvp]            E-face plane, then N-face plane
 //   kv             [nvp]               face k|k+1; row nz-1 is zero (no flux

@@ -33,14 +33,14 @@
 // index arithmetic per element and sweep; single places 8 apart fetched each
 // line up to four times).
 //
-// Measured (V-cycle entry point, kernel by kernel against patches, us): C12 x 10
-// float64 62 / 35, C24 x 30 float32 89 / 47, C64 x 30 144 / 85, C192 x 70 (C24,
-// C12 and C6 on patches) 742 / 704. A leg now takes 5 to 12 us, of which 2 are
-// the launch, 1 to 2 the first loads and 0.8 to 1.5 each sweep.
+// Measured (V-cycle entry point, kernel by kernel with conversion passes against
+// patches, us): C12 x 10 float64 64 / 30, C24 x 30 float32 90 / 45, C64 x 30 124 /
+// 70, C192 x 70 (C24, C12 and C6 on patches) 738 / 667. A leg takes 5 to 12 us, of
+// which 2 are the launch, 1 to 2 the first loads and 0.8 to 1.5 each sweep.
 //
 // Every value is formed by the operations of k_sweep and k_resid_restrict in
 // their order (fused multiply-adds written out as the compiler forms them
-// there), so the results are the same bits.
+// there), so the results are the same bits, infinities and NaN among them.
 #pragma once
 #include "columns.hpp"
 
